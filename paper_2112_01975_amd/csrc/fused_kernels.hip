@@ -487,9 +487,8 @@ __global__ __launch_bounds__(FTX * TY) void k_fused3(const S *__restrict__ A, S 
         const uint32_t l3 = MM ? links_at(si, zs3) : 0u;
         const uint32_t b3 = MM && need3 ? qlo_at(si, zs3) : 0u;
 
-        const unsigned zoff = (unsigned)(nxy * (z < g.nz ? z : 0)) * SB;
-        const bool act = own && z < g.nz &&
-                         !(MASK && (plane_flags(z) & 1u) && ((fm.links[(si.v[1][1] + zoff) / SB] >> LINK_SELF) & 1u));
+        const unsigned zoff = (unsigned)(nxy * wrapi(z, g.nz)) * SB;
+        const bool act = own && !(MASK && (plane_flags(z) & 1u) && ((fm.links[(si.v[1][1] + zoff) / SB] >> LINK_SELF) & 1u));
         if constexpr (REPULL) {
             // plane z again: the loads are in flight during the stencil (the halo node of
             // plane z+3 is then pulled when it is staged, so that both sets of loads are

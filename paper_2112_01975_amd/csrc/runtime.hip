@@ -347,15 +347,15 @@ int lbm_create(const lbm_params *p, lbm_ctx **out) {
     if (c->D == 3 && !env_int("LBM2P_TWO_PASS", 0) && (!few_items || env_int("LBM2P_FUSED", 0))) {
         // Chunk length for a run of len planes. Each work item (tile x chunk) marches its
         // planes after a five-plane prologue; items run in rounds of one per CU. The number
-        // of chunks minimises rounds x (planes per chunk + 6), chunks of >= 16 planes: long
+        // of chunks minimises rounds x (planes per chunk + 6), chunks of >= least planes: long
         // chunks, but no last round that leaves most CUs idle (288 tiles on 256 CUs in one
         // chunk would take two full rounds' time for 1.1 rounds' work). Chunks stay within
         // 320 planes: over longer marches neighbouring tiles drift apart in z and the halo
         // lines they share leave L2 between the two reads (600^3: 600-plane chunks 14.7,
         // 300-plane chunks 15.2 GLUPS).
-        auto chunk = [&](int len) {
+        auto chunk = [&](int len, int least) {
             long long best = 1, cost = -1;
-            for (long long nzc = std::max(1, (len + 319) / 320); nzc <= std::max(1, len / 16); ++nzc) {
+            for (long long nzc = std::max(1, (len + 319) / 320); nzc <= std::max(1, len / least); ++nzc) {
                 const long long rounds = (tiles * nzc + cus - 1) / cus;
                 const long long c = rounds * ((len + nzc - 1) / nzc + 6);
                 if (cost < 0 || c < cost) { cost = c; best = nzc; }
@@ -377,22 +377,27 @@ int lbm_create(const lbm_params *p, lbm_ctx **out) {
                                                 : nullptr;
             const int nz = c->g.nz;
             if (!c->masked) {
-                if (plain) c->segs.push_back({plain, fused_grid(c->g, tx, ty, chunk(nz), 0, nz)});
+                if (plain) c->segs.push_back({plain, fused_grid(c->g, tx, ty, chunk(nz, 16), 0, nz)});
             } else if (walls) {
                 // A plane is collided, staged and pulled from within three planes of itself,
                 // so planes with no solid node in z-3..z+3 run the unmasked kernel; maximal
-                // runs of equal kind become the launches of a step
+                // runs of equal kind become the launches of a step. A run near walls is thin, so
+                // its chunks may be: on 128^3 with posts 18 planes tall, 32 tiles of one 21-plane
+                // chunk left 224 CUs idle (FP64: 0.96 ms a step; 3-plane chunks, one run: 0.42 ms)
                 const size_t nxy = (size_t)c->g.nx * c->g.ny;
                 std::vector<char> has(nz, 0), near(nz, 0);
                 for (int z = 0; z < nz; ++z)
                     for (size_t q = 0; q < nxy && !has[z]; ++q) has[z] = p->mask[(size_t)z * nxy + q] ? 1 : 0;
                 for (int z = 0; z < nz; ++z)
                     for (int d = -3; d <= 3 && !near[z]; ++d) near[z] = has[((z + d) % nz + nz) % nz];
-                for (int zb = 0; zb < nz;) {
+                // (z is periodic: a floor at z = 0 and its planes below z = nz are one run)
+                int z0 = 0;
+                for (int z = 1; z < nz && !z0; ++z) z0 = near[z] != near[z - 1] ? z : 0;
+                for (int zb = z0; zb < z0 + nz;) {
                     int ze = zb + 1;
-                    while (ze < nz && near[ze] == near[zb]) ++ze;
-                    const FusedLaunch fn = near[zb] || !plain ? walls : plain;
-                    c->segs.push_back({fn, fused_grid(c->g, tx, ty, chunk(ze - zb), zb, ze)});
+                    while (ze < z0 + nz && near[ze % nz] == near[zb % nz]) ++ze;
+                    const FusedLaunch fn = near[zb % nz] || !plain ? walls : plain;
+                    c->segs.push_back({fn, fused_grid(c->g, tx, ty, chunk(ze - zb, 2), zb, ze)});
                     zb = ze;
                 }
             }

@@ -498,6 +498,32 @@ def test_fused_step_plane_runs_match_two_pass(precision, monkeypatch):
         assert max_rel(fused[0], two[0]) < 1e-5 and np.abs(fused[1] - two[1]).max() < 1e-6
 
 
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("solid_planes", [(0,), (62,), (1, 33)])
+def test_fused_plane_run_across_the_periodic_boundary_matches_two_pass(solid_planes, precision, monkeypatch):
+    # the planes near a solid at either end of z form one run that wraps (from nz - 3 to 3 for a
+    # floor at 0), in z-chunks of a few planes; one chunk then holds planes on both sides of z = 0
+    nx, ny, nz = 40, 20, 64
+    m = np.zeros((nz, ny, nx), np.uint8)
+    for z in solid_planes:
+        m[z, :, ::2] = 1
+    case = Case(3, nx, ny, nz, eos=T.PR, a=0.005046, acentric=0.344, T_reduced=0.6, rho_wall=0.0102306,
+                mask=m.ravel())
+    rv, rl = case.coexistence()
+    rho0 = L.drop(nx, ny, nz, 8.0, rl, rv, 5.0, centre=(20.0, 10.0, 48.0), noise=1e-5, seed=1012)
+    rho0 = np.where(m.ravel().astype(bool), rv, rho0)
+    rr = rv if precision else 0.0
+    fused = run_gpu(case, rho0, None, 30, precision=precision, rho_ref=rr)
+    monkeypatch.setenv("LBM2P_FUSED_TZ", "5")
+    ragged = run_gpu(case, rho0, None, 30, precision=precision, rho_ref=rr)
+    monkeypatch.setenv("LBM2P_TWO_PASS", "1")
+    two = run_gpu(case, rho0, None, 30, precision=precision, rho_ref=rr)
+    tol, utol = (1e-12, 1e-13) if precision == 0 else (1e-5, 1e-6)
+    for r, u, _ in (fused, ragged):
+        assert np.all(np.isfinite(r))
+        assert max_rel(r, two[0]) < tol and np.abs(u - two[1]).max() < utol
+
+
 # ---------------------------------------------------------------- batched sweep
 def _sweep_cases(n, steps_len_lo=32, steps_len_hi=96):
     """A reduced temperature sweep: D2Q9 4 x L flat interfaces, FP64 from T/Tc >= 0.95."""
