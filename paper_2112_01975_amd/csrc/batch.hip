@@ -43,6 +43,7 @@ struct CaseDesc {
     void *A, *B;    // population lattices (A = current)
     void *frho, *fpsi, *fg;   // fields in compute precision: rho, s*psi, g[D]
     const uint8_t *mask;      // nullable
+    uint32_t *links;          // solid-neighbour bits (masked cases)
     double *totals;           // 5 slots: mass, j, domain-error count (FP64)
     Params<double> pd;
     Params<float> pf;
@@ -720,11 +721,14 @@ int lbm_batch_create(const lbm_params *cases, int ncases, lbm_batch **out) {
         cd.fg = dalloc((size_t)cd.D * N * s);
         cd.totals = (double *)dalloc(8 * sizeof(double));
         cd.mask = nullptr;
+        cd.links = nullptr;
         if (!cd.A || !cd.B || !cd.frho || !cd.fpsi || !cd.fg || !cd.totals) { free_batch(b); return bfail(nullptr, LBM_E_NOMEM, "device allocation failed"); }
         if (p.mask) {
             uint8_t *m = (uint8_t *)dalloc(N);
             if (!m || hipMemcpy(m, p.mask, N, hipMemcpyHostToDevice) != hipSuccess) { free_batch(b); return bfail(nullptr, LBM_E_HIP, "mask upload failed"); }
             cd.mask = m;
+            cd.links = (uint32_t *)dalloc(N * sizeof(uint32_t));
+            if (!cd.links) { free_batch(b); return bfail(nullptr, LBM_E_NOMEM, "device allocation failed"); }
         }
         if (p.rho_wall_field) {   // per-node wall densities of this case
             void *w = cd.fp64 ? (void *)upload_wall_field<double>(p.rho_wall_field, cd.g)
@@ -737,6 +741,7 @@ int lbm_batch_create(const lbm_params *cases, int ncases, lbm_batch **out) {
         b->params[c].mask = nullptr;
         b->params[c].rho_wall_field = nullptr;
         b->ks[c] = kernel_set(cd.D, cd.fp64, cd.mask != nullptr);
+        if (cd.mask) b->ks[c].links(b->stream, cd.mask, cd.links, cd.g);
         b->nblk[c] = moment_block_count(cd.D, cd.g);
         max_nblk = std::max(max_nblk, b->nblk[c]);
         b->io_elems = std::max(b->io_elems, (size_t)(1 + cd.D) * N);
@@ -1019,16 +1024,15 @@ int lbm_batch_moments(lbm_batch *b, int icase, double *rho, double *U, double to
     void *A = current_A(b, icase, parity);
     const void *prm = cd.fp64 ? (const void *)&cd.pd : (const void *)&cd.pf;
     const size_t N = (size_t)cd.g.N;
-    // the two-pass moment kernel refreshes rho and g in the case's fields and writes partials
-    b->ks[icase].moments(b->stream, A, cd.g, cd.mask, prm, cd.frho, cd.fg, b->partials);
+    // one moment pass: totals, rho and the bare velocity; the velocity kernel adds the half force
+    double *orho = rho ? b->io : nullptr, *oU = U ? b->io + N : nullptr;
+    b->ks[icase].moments(b->stream, A, cd.g, cd.links, prm, U ? cd.frho : nullptr, nullptr, orho, oU, b->partials);
+    if (U) b->ks[icase].velocity(b->stream, cd.g, cd.links, prm, cd.frho, oU);
     launch_reduce(b->stream, b->partials, b->nblk[icase], b->rscratch, b->d_tot);
     double t[5];
     BHIP(b, hipMemcpyAsync(t, b->d_tot, 5 * sizeof(double), hipMemcpyDeviceToHost, b->stream));
-    if (rho || U) {
-        b->ks[icase].output(b->stream, A, cd.g, cd.mask, prm, cd.frho, cd.fg, b->io, b->io + N);
-        if (rho) BHIP(b, hipMemcpyAsync(rho, b->io, N * sizeof(double), hipMemcpyDeviceToHost, b->stream));
-        if (U) BHIP(b, hipMemcpyAsync(U, b->io + N, cd.D * N * sizeof(double), hipMemcpyDeviceToHost, b->stream));
-    }
+    if (rho) BHIP(b, hipMemcpyAsync(rho, orho, N * sizeof(double), hipMemcpyDeviceToHost, b->stream));
+    if (U) BHIP(b, hipMemcpyAsync(U, oU, cd.D * N * sizeof(double), hipMemcpyDeviceToHost, b->stream));
     BHIP(b, hipGetLastError());
     BHIP(b, hipStreamSynchronize(b->stream));
     if (totals) for (int k = 0; k < 4; ++k) totals[k] = t[k];

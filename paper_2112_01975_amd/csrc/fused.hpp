@@ -32,7 +32,7 @@ FusedGrid fused_grid(const Geom &g, int tx, int ty, int tz, int zb, int ze);
 std::vector<FusedGrid> fused_windows(const FusedGrid &fg, int window);
 
 // Solid geometry for the fused step (nullptr without solid nodes):
-//   links[n]  per-node solid-neighbour bits from fused_links;
+//   links[n]  per-node solid-neighbour bits from KernelSet::links;
 //   pflags[z] bit 0: plane z has a solid node, bit 1: planes z-1..z+1 have one;
 //   qlo[n]    with interpolated walls only: bit i when the wall link crossed by
 //             population i has q < 1/2 (fused_qlo).
@@ -53,9 +53,6 @@ struct FusedSeg {
     FusedLaunch fn;
     FusedGrid fg;
 };
-
-// bit i of links[n]: the source node n - c_i of population i is solid; bit 27: n is solid
-void fused_links(hipStream_t s, const uint8_t *mask, uint32_t *links, const Geom &g);
 
 // the q < 1/2 bits from the links and the device wall fractions ([Q][qs], compute precision)
 void fused_qlo(hipStream_t s, const uint32_t *links, const void *lq, bool fp64, uint32_t *qlo, const Geom &g);

@@ -192,10 +192,6 @@ template <class S, int P> struct LatticeK {
     }
 };
 
-// Solid-neighbour bits of a node (built once per geometry by k_links): bit i is set
-// when the source node r - c_i of population i is solid, bit LINK_SELF when r is.
-constexpr int LINK_SELF = 27;
-
 template <int i, class S, class C, bool MASK, class LT>
 __device__ __forceinline__ C pull(const LT &A, uint32_t lm, const Stencil &st, const unsigned (&zs)[3]) {
     constexpr int cx = Lat<3>::c(i, 0), cy = Lat<3>::c(i, 1), cz = Lat<3>::c(i, 2);
@@ -690,24 +686,6 @@ void launch_fused(hipStream_t s, const void *A, void *B, const Geom &g, const Fu
                        (const S *)A, (S *)B, g, fm, *(const Params<C> *)prm, fg);
 }
 
-__global__ void k_links(const uint8_t *__restrict__ mask, uint32_t *__restrict__ links, Geom g) {
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= g.N) return;
-    const int x = n % g.px, y = (n / g.px) % g.ny, z = n / (g.px * g.ny);
-    if (x >= g.nx) {   // row padding
-        links[n] = 0u;
-        return;
-    }
-    uint32_t b = mask[n] ? (1u << LINK_SELF) : 0u;
-    static_for<1, 27>([&](auto I) {
-        constexpr int i = decltype(I)::value;
-        const int s = wrapi(x - Lat<3>::c(i, 0), g.nx) +
-                      g.px * (wrapi(y - Lat<3>::c(i, 1), g.ny) + g.ny * wrapi(z - Lat<3>::c(i, 2), g.nz));
-        if (mask[s]) b |= 1u << i;
-    });
-    links[n] = b;
-}
-
 // bit i set when population i of fluid node n crosses a wall link whose fraction (stored
 // under opp(i)) is below 1/2, compared in the compute precision C of the step
 template <class C>
@@ -725,10 +703,6 @@ __global__ void k_qlo(const uint32_t *__restrict__ links, const C *__restrict__ 
 }
 
 }  // namespace
-
-void fused_links(hipStream_t s, const uint8_t *mask, uint32_t *links, const Geom &g) {
-    hipLaunchKernelGGL(k_links, dim3((g.N + 255) / 256), dim3(256), 0, s, mask, links, g);
-}
 
 void fused_qlo(hipStream_t s, const uint32_t *links, const void *lq, bool fp64, uint32_t *qlo, const Geom &g) {
     if (fp64)

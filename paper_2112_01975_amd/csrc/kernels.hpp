@@ -49,21 +49,26 @@ struct KernelSet {
     // re-solved so that the interpolated pull returns the same equilibria
     void (*init)(hipStream_t, void *A, const Geom &, const uint8_t *mask, const void *params, void *rho,
                  const double *rho0, const double *U0);
-    // rho and g = rho u^3 of the current state, per-workgroup FP64 partials
-    void (*moments)(hipStream_t, const void *A, const Geom &, const uint8_t *mask, const void *params,
-                    void *rho, void *g, double *partials);
+    // solid-neighbour bits of every node from the mask: bit i of links[n] when the source node
+    // n - c_i of population i is solid, bit 27 when n is (row padding 0)
+    void (*links)(hipStream_t, const uint8_t *mask, uint32_t *links, const Geom &);
+    // moment pass over the current state, per-workgroup FP64 partials; every field is optional
+    // (nullptr): rho and g = rho u^3 in compute precision and the pitched layout; out_rho and the
+    // bare velocity out_U = j / rho in FP64 and the user layout (rows of nx)
+    void (*moments)(hipStream_t, const void *A, const Geom &, const uint32_t *links, const void *params,
+                    void *rho, void *g, double *out_rho, double *out_U, double *partials);
     // one collide-stream step A -> B (reads rho, g written by moments)
-    void (*collide)(hipStream_t, const void *A, void *B, const Geom &, const uint8_t *mask, const void *params,
+    void (*collide)(hipStream_t, const void *A, void *B, const Geom &, const uint32_t *links, const void *params,
                     const void *rho, const void *g);
     // one collide-stream step A -> B in a single pass, rho and g from the tile's own pulls
     // (D2Q9; nullptr for D3Q27)
-    void (*single)(hipStream_t, const void *A, void *B, const Geom &, const uint8_t *mask, const void *params);
-    // rho and U = u + S/(2 rho) of the current state in FP64 (reads rho, g)
-    void (*output)(hipStream_t, const void *A, const Geom &, const uint8_t *mask, const void *params,
-                   const void *rho, const void *g, double *out_rho, double *out_U);
+    void (*single)(hipStream_t, const void *A, void *B, const Geom &, const uint32_t *links, const void *params);
+    // adds S/(2 rho) to the bare velocity that moments left in out_U (reads rho)
+    void (*velocity)(hipStream_t, const Geom &, const uint32_t *links, const void *params, const void *rho,
+                     double *out_U);
     // discrete pressure tensor of the state in A (reads rho written by moments), FP64
     // [D(D+1)/2][N] into out
-    void (*pressure)(hipStream_t, const void *A, const Geom &, const uint8_t *mask, const void *params,
+    void (*pressure)(hipStream_t, const void *A, const Geom &, const uint32_t *links, const void *params,
                      const void *rho, double *out);
     int moment_blocks;  // filled by kernel_blocks()
 };

@@ -37,7 +37,7 @@ struct lbm_ctx {
     void *A = nullptr, *B = nullptr; // population lattices
     void *rho = nullptr, *gfl = nullptr;
     uint8_t *mask = nullptr;
-    uint32_t *links = nullptr;       // solid-neighbour bits for the fused step (masked only)
+    uint32_t *links = nullptr;       // solid-neighbour bits (masked only)
     uint32_t *pflags = nullptr;      // per-plane solid flags for the fused step (masked only)
     uint32_t *qlo = nullptr;         // q < 1/2 bits of the wall links for the fused step (link_q only)
     void *wall = nullptr;            // per-node wall densities in compute precision (optional)
@@ -133,10 +133,20 @@ int reduce_rows(lbm_ctx *c, const double *rows, int n, double host[5]) {
     return LBM_OK;
 }
 
-// mass/momentum of the current state -> host[5]; also the domain-error count
-int reduce_state(lbm_ctx *c, double host[5]) {
-    c->ks.moments(c->stream, c->A, c->g, c->mask, params_ptr(c), c->rho, c->gfl, c->partials);
+// mass/momentum of the current state -> host[5]; also the domain-error count. rho (nullable):
+// the device field that receives the densities
+int reduce_state(lbm_ctx *c, double host[5], void *rho = nullptr) {
+    c->ks.moments(c->stream, c->A, c->g, c->links, params_ptr(c), rho, nullptr, nullptr, nullptr, c->partials);
     return reduce_rows(c, c->partials, c->nblk, host);
+}
+
+// rho and U of the current state in FP64 and the user layout (each nullable), and the moment
+// pass's partial rows. One pass over the populations leaves rho and the bare velocity, one over
+// rho adds the half force (256^3: FP32 0.68 ms, FP64 1.25 ms; reading the populations again for
+// the velocity took 1.03 and 2.04 ms, and padded rows a repacking pass besides).
+void output_fields(lbm_ctx *c, double *partials, double *rho, double *U) {
+    c->ks.moments(c->stream, c->A, c->g, c->links, params_ptr(c), U ? c->rho : nullptr, nullptr, rho, U, partials);
+    if (U) c->ks.velocity(c->stream, c->g, c->links, params_ptr(c), c->rho, U);
 }
 
 // Watchdog check. After a single-pass step it reduces the rows that step wrote while pulling
@@ -167,10 +177,10 @@ void fused_step(lbm_ctx *c) {
 // the two-pass step, or the D2Q9 single pass, from lattice a into b on stream s
 void unfused_step(lbm_ctx *c, hipStream_t s, const void *a, void *b) {
     if (c->single) {
-        c->ks.single(s, a, b, c->g, c->mask, params_ptr(c));
+        c->ks.single(s, a, b, c->g, c->links, params_ptr(c));
     } else {
-        c->ks.moments(s, a, c->g, c->mask, params_ptr(c), c->rho, c->gfl, c->partials);
-        c->ks.collide(s, a, b, c->g, c->mask, params_ptr(c), c->rho, c->gfl);
+        c->ks.moments(s, a, c->g, c->links, params_ptr(c), c->rho, c->gfl, nullptr, nullptr, c->partials);
+        c->ks.collide(s, a, b, c->g, c->links, params_ptr(c), c->rho, c->gfl);
     }
 }
 
@@ -436,7 +446,8 @@ int lbm_create(const lbm_params *p, lbm_ctx **out) {
     for (FusedSeg &sg : c->segs) sg.fg.partials = nullptr;   // set once fpart exists
     const size_t pop = (size_t)c->Q * (size_t)c->g.qs * c->sbytes;
     if (hipMalloc(&c->A, pop) != hipSuccess || hipMalloc(&c->B, pop) != hipSuccess ||
-        hipMalloc(&c->rho, N * cbytes) != hipSuccess || hipMalloc(&c->gfl, (size_t)c->D * N * cbytes) != hipSuccess ||
+        hipMalloc(&c->rho, N * cbytes) != hipSuccess ||
+        (!c->fused && !c->single && hipMalloc(&c->gfl, (size_t)c->D * N * cbytes) != hipSuccess) ||   // two-pass step only
         hipMalloc((void **)&c->partials, (size_t)c->nblk * kPartialSlots * sizeof(double)) != hipSuccess ||
         hipMalloc((void **)&c->rscratch, (size_t)std::max(reduce_scratch_rows(c->nblk), reduce_scratch_rows(c->nfslots)) *
                                              kPartialSlots * sizeof(double)) != hipSuccess ||
@@ -483,12 +494,13 @@ int lbm_create(const lbm_params *p, lbm_ctx **out) {
             free_ctx(c);
             return fail(nullptr, LBM_E_HIP, std::string("mask upload failed: ") + hipGetErrorString(e));
         }
-        if (c->fused) {   // solid-neighbour bits: one word per node instead of 27 mask reads per pull
-            if (hipMalloc((void **)&c->links, N * sizeof(uint32_t)) != hipSuccess) {
-                free_ctx(c);
-                return fail(nullptr, LBM_E_NOMEM, "device allocation of the link mask failed");
-            }
-            fused_links(c->stream, c->mask, c->links, c->g);
+        // solid-neighbour bits: one word per node instead of a mask read per pull
+        if (hipMalloc((void **)&c->links, N * sizeof(uint32_t)) != hipSuccess) {
+            free_ctx(c);
+            return fail(nullptr, LBM_E_NOMEM, "device allocation of the link mask failed");
+        }
+        c->ks.links(c->stream, c->mask, c->links, c->g);
+        if (c->fused) {
             if (c->lq) {   // which partner each interpolated wall link reads
                 if (hipMalloc((void **)&c->qlo, N * sizeof(uint32_t)) != hipSuccess) {
                     free_ctx(c);
@@ -510,10 +522,10 @@ int lbm_create(const lbm_params *p, lbm_ctx **out) {
                 free_ctx(c);
                 return fail(nullptr, LBM_E_HIP, std::string("plane flag upload failed: ") + hipGetErrorString(e));
             }
-            if ((e = hipStreamSynchronize(c->stream)) != hipSuccess || (e = hipGetLastError()) != hipSuccess) {
-                free_ctx(c);
-                return fail(nullptr, LBM_E_HIP, std::string("link mask failed: ") + hipGetErrorString(e));
-            }
+        }
+        if ((e = hipStreamSynchronize(c->stream)) != hipSuccess || (e = hipGetLastError()) != hipSuccess) {
+            free_ctx(c);
+            return fail(nullptr, LBM_E_HIP, std::string("link mask failed: ") + hipGetErrorString(e));
         }
     }
     *out = c;
@@ -580,15 +592,15 @@ int lbm_step_timed(lbm_ctx *c, int64_t n, double ms[3], int64_t launches[2]) {
     for (int64_t t = 0; t < n; ++t) {
         HIP_OR_FAIL(c, hipEventRecord(ev[0], c->stream));
         if (!c->fused && !c->single)
-            c->ks.moments(c->stream, c->A, c->g, c->mask, params_ptr(c), c->rho, c->gfl, c->partials);
+            c->ks.moments(c->stream, c->A, c->g, c->links, params_ptr(c), c->rho, c->gfl, nullptr, nullptr, c->partials);
         HIP_OR_FAIL(c, hipEventRecord(ev[1], c->stream));
         if (c->fused) {
             fused_step(c);
             c->folded = c->fold;
         } else if (c->single) {
-            c->ks.single(c->stream, c->A, c->B, c->g, c->mask, params_ptr(c));
+            c->ks.single(c->stream, c->A, c->B, c->g, c->links, params_ptr(c));
         } else {
-            c->ks.collide(c->stream, c->A, c->B, c->g, c->mask, params_ptr(c), c->rho, c->gfl);
+            c->ks.collide(c->stream, c->A, c->B, c->g, c->links, params_ptr(c), c->rho, c->gfl);
         }
         ++c->steps;
         HIP_OR_FAIL(c, hipEventRecord(ev[2], c->stream));
@@ -618,22 +630,16 @@ int lbm_step_timed(lbm_ctx *c, int64_t n, double ms[3], int64_t launches[2]) {
 int lbm_moments(lbm_ctx *c, double *rho, double *U, double totals[4]) {
     if (!c) return fail(c, LBM_E_INVAL, "context is NULL");
     if (!c->initialized) return fail(c, LBM_E_STATE, "lbm_moments before lbm_init_fields");
+    const size_t Nu = user_nodes(c);
+    double *orho = rho ? c->io : nullptr, *oU = U ? c->io + Nu : nullptr;
+    output_fields(c, c->partials, orho, oU);
     double t[5];
-    int rc = reduce_state(c, t);    // also refreshes rho and g of the current state
+    const int rc = reduce_rows(c, c->partials, c->nblk, t);
     if (rc) return rc;
     if (totals) for (int k = 0; k < 4; ++k) totals[k] = t[k];
-    if (rho || U) {
-        const size_t N = (size_t)c->g.N;
-        c->ks.output(c->stream, c->A, c->g, c->mask, params_ptr(c), c->rho, c->gfl, c->io, c->io + N);
-        HIP_OR_FAIL(c, hipGetLastError());
-        const size_t Nu = user_nodes(c);
-        if (rho) HIP_OR_FAIL(c, copy_rows(c, rho, c->io, sizeof(double), hipMemcpyDeviceToHost));
-        if (U)
-            for (int a = 0; a < c->D; ++a)
-                HIP_OR_FAIL(c, copy_rows(c, U + (size_t)a * Nu, c->io + N + (size_t)a * N, sizeof(double),
-                                         hipMemcpyDeviceToHost));
-        HIP_OR_FAIL(c, hipStreamSynchronize(c->stream));
-    }
+    if (rho) HIP_OR_FAIL(c, hipMemcpyAsync(rho, orho, Nu * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+    if (U) HIP_OR_FAIL(c, hipMemcpyAsync(U, oU, (size_t)c->D * Nu * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+    if (rho || U) HIP_OR_FAIL(c, hipStreamSynchronize(c->stream));
     return LBM_OK;
 }
 
@@ -648,26 +654,8 @@ int lbm_moments_noalloc(lbm_ctx *c, double *rho, double *U, double *totals) {
                                         " (use lbm_moments)");
     if (!c->initialized) return fail(c, LBM_E_STATE, "lbm_moments_noalloc before lbm_init_fields");
     double *part = c->scratch, *tree = c->scratch + (size_t)c->nblk * kPartialSlots;
-    c->ks.moments(c->stream, c->A, c->g, c->mask, params_ptr(c), c->rho, c->gfl, part);
+    output_fields(c, part, rho, U);
     if (totals) launch_reduce(c->stream, part, c->nblk, tree, totals);
-    if (rho || U) {
-        // unpadded rows: the output pass writes the caller's buffers (the context's staging
-        // takes a field the caller did not ask for); padded rows: staging, then a repack
-        const size_t N = (size_t)c->g.N;
-        const bool padded = c->g.px != c->g.nx;
-        c->ks.output(c->stream, c->A, c->g, c->mask, params_ptr(c), c->rho, c->gfl,
-                     (padded || !rho) ? c->io : rho, (padded || !U) ? c->io + N : U);
-        if (padded) {
-            const long long words = 2LL * c->g.nx, sp = 2LL * c->g.px, yz = (long long)c->g.ny * c->g.nz;
-            auto repack = [&](const double *src, double *dst, long long rows_) {
-                const dim3 grid((unsigned)((words * rows_ + 255) / 256));
-                hipLaunchKernelGGL(k_repitch, grid, dim3(256), 0, c->stream, (const uint32_t *)src, (uint32_t *)dst,
-                                   words, sp, words, rows_);
-            };
-            if (rho) repack(c->io, rho, yz);
-            if (U) repack(c->io + N, U, c->D * yz);   // the D components are consecutive in both layouts
-        }
-    }
     HIP_OR_FAIL(c, hipGetLastError());
     return LBM_OK;
 }
@@ -682,9 +670,9 @@ int lbm_pressure_tensor(lbm_ctx *c, double *P) {
         return fail(c, LBM_E_NOMEM, "device allocation of the pressure tensor failed");
     }
     double t[5];
-    int rc = reduce_state(c, t);    // rho of the current state
+    int rc = reduce_state(c, t, c->rho);    // rho of the current state
     if (rc) return rc;
-    c->ks.pressure(c->stream, c->A, c->g, c->mask, params_ptr(c), c->rho, c->ptens);
+    c->ks.pressure(c->stream, c->A, c->g, c->links, params_ptr(c), c->rho, c->ptens);
     HIP_OR_FAIL(c, hipGetLastError());
     for (int k = 0; k < nc; ++k)
         HIP_OR_FAIL(c, copy_rows(c, P + (size_t)k * Nu, c->ptens + (size_t)k * N, sizeof(double), hipMemcpyDeviceToHost));

@@ -79,36 +79,64 @@ template <class T> __device__ __forceinline__ void st_nt_at(T *__restrict__ base
     __builtin_nontemporal_store(v, (T *)((char *)base + idx * (unsigned)sizeof(T)));
 }
 
-// Population i arriving at fluid node n whose source n - c_i is solid. Halfway bounce-back
-// returns the opposite post-collision population of n itself. With wall fractions lq
-// ([Q][qs]; the link n -> n - c_i is stored under opp(i)) the linearly interpolated
-// bounce-back of Bouzidi et al. that the paper uses for curved walls (Sec. 4.5, 5.3):
+// Solid-neighbour bits of a node (one word per node, built once per geometry): bit i is set
+// when the source node n - c_i of population i is solid, bit LINK_SELF when n is.
+constexpr int LINK_SELF = 27;
+__device__ __forceinline__ bool link_solid(uint32_t lm) { return (lm >> LINK_SELF) & 1u; }
+
+// Population i arriving at fluid node n (links lm) whose source n - c_i is solid. Halfway
+// bounce-back returns the opposite post-collision population of n itself, `back`. With wall
+// fractions lq ([Q][qs]; the link n -> n - c_i is stored under opp(i)) the linearly
+// interpolated bounce-back of Bouzidi et al. that the paper uses for curved walls (Sec. 4.5, 5.3):
 //   q <  1/2: 2q A_opp(n) + (1 - 2q) A_opp(n + c_i)   (A_opp(n) when n + c_i is solid)
 //   q >= 1/2: A_opp(n) / (2q) + (1 - 1/(2q)) A_i(n)
 // Both weight pairs sum to one and w_i = w_opp(i), so FP32 deviations interpolate as is.
 template <int D, int i, class S, class C>
-__device__ __forceinline__ C wall_pull(const S *__restrict__ A, long long qs, const uint8_t *__restrict__ mask,
-                                       const C *__restrict__ lq, const Nbr<D> &nb, int n) {
+__device__ __forceinline__ C wall_pull(const S *__restrict__ A, long long qs, uint32_t lm, const C *__restrict__ lq,
+                                       const Nbr<D> &nb, int n, C back) {
     constexpr int o = opp<D>(i);
-    const C back = C(ld_at(A + o * qs, (unsigned)n));
-    if (!lq) return back;
     const C q = ld_at(lq + o * qs, (unsigned)n);
     if (q < C(0.5)) {
         constexpr int cx = Lat<D>::c(i, 0), cy = Lat<D>::c(i, 1), cz = Lat<D>::c(i, 2);
-        const unsigned b = (unsigned)nb.at(cx, cy, cz);
-        const C behind = ld_at(mask, b) ? back : C(ld_at(A + o * qs, b));
+        const C behind = (lm >> o) & 1u ? back : C(ld_at(A + o * qs, (unsigned)nb.at(cx, cy, cz)));
         return C(2) * q * back + (C(1) - C(2) * q) * behind;
     }
     const C h2q = C(2) * q;
     return back / h2q + (C(1) - C(1) / h2q) * C(ld_at(A + i * qs, (unsigned)n));
 }
 
-// pull gather of the Q populations arriving at node n (= r) at this time step; lq: wall
-// fractions for interpolated bounce-back, or nullptr (halfway)
+// Pull gather of the Q populations arriving at fluid node n with links lm at this time step; lq:
+// wall fractions for interpolated bounce-back, or nullptr (halfway). The word of links makes
+// every pull one load at a selected address: a mask byte per source node cost as many loads
+// again, each before a branch (512x256x256 with pillars, FP32: moment pass 1.30 ms so, 0.83
+// with the links).
+template <int D, class S, class C, bool MASK>
+__device__ __forceinline__ void gather_links(const S *__restrict__ A, long long qs, uint32_t lm, const Nbr<D> &nb, int n,
+                                             C (&h)[Lat<D>::Q], const C *__restrict__ lq) {
+    static_for<0, Lat<D>::Q>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        constexpr int cx = Lat<D>::c(i, 0), cy = Lat<D>::c(i, 1), cz = Lat<D>::c(i, 2);
+        if constexpr (i == 0) {
+            h[0] = C(ld_at(A, (unsigned)n));
+        } else if constexpr (!MASK) {
+            h[i] = C(ld_at(A + i * qs, (unsigned)nb.at(-cx, -cy, -cz)));
+        } else {
+            const bool w = (lm >> i) & 1u;
+            const S *a = A + (w ? opp<D>(i) * qs : i * qs) + (w ? n : nb.at(-cx, -cy, -cz));
+            h[i] = C(*a);
+        }
+    });
+    if (MASK && lq && (lm & ((1u << LINK_SELF) - 1u)))
+        static_for<1, Lat<D>::Q>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            if ((lm >> i) & 1u) h[i] = wall_pull<D, i, S, C>(A, qs, lm, lq, nb, n, h[i]);
+        });
+}
+
+// The same pull with the solid flags of a mask and halfway walls (the batched sweep).
 template <int D, class S, class C, bool MASK>
 __device__ __forceinline__ void gather(const S *__restrict__ A, long long qs, const uint8_t *__restrict__ mask,
-                                       const Nbr<D> &nb, int n, C (&h)[Lat<D>::Q],
-                                       const C *__restrict__ lq = nullptr) {
+                                       const Nbr<D> &nb, int n, C (&h)[Lat<D>::Q]) {
     static_for<0, Lat<D>::Q>([&](auto I) {
         constexpr int i = decltype(I)::value;
         constexpr int cx = Lat<D>::c(i, 0), cy = Lat<D>::c(i, 1), cz = Lat<D>::c(i, 2);
@@ -117,14 +145,13 @@ __device__ __forceinline__ void gather(const S *__restrict__ A, long long qs, co
         } else {
             const unsigned s = (unsigned)nb.at(-cx, -cy, -cz);
             if constexpr (MASK) {
-                h[i] = ld_at(mask, s) ? wall_pull<D, i, S, C>(A, qs, mask, lq, nb, n) : C(ld_at(A + i * qs, s));
+                h[i] = ld_at(mask, s) ? C(ld_at(A + opp<D>(i) * qs, (unsigned)n)) : C(ld_at(A + i * qs, s));
             } else {
                 h[i] = C(ld_at(A + i * qs, s));
             }
         }
     });
 }
-
 
 // sum h and j = sum c h in a fixed order (pass 1 and pass 2 must agree bit for bit)
 template <int D, class C>

@@ -19,6 +19,8 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include <algorithm>
+
 #include "kernels.hpp"
 #include "lattice.hpp"
 #include "step_common.hpp"
@@ -58,43 +60,70 @@ __device__ __forceinline__ void block_sum5(double (&v)[kPartialSlots], double *_
 }
 
 // ------------------------------------------------------------------ pass 1
+// Moment pass. Only what the caller uses is written: the two-pass step and the pressure tensor
+// take rho (and g) in the pitched layout, the output of fields rho and the bare velocity in
+// the user layout, a watchdog check the partials alone.
 template <int D, class S, class C, bool MASK>
-__global__ __launch_bounds__(256) void k_moments(const S *__restrict__ A, Geom g, const uint8_t *__restrict__ mask,
+__global__ __launch_bounds__(256) void k_moments(const S *__restrict__ A, Geom g, const uint32_t *__restrict__ links,
                                                  Params<C> p, C *__restrict__ rho_out, C *__restrict__ gf,
+                                                 double *__restrict__ out_rho, double *__restrict__ out_U,
                                                  double *__restrict__ partials) {
     const int tx = threadIdx.x & (TX - 1), ty = threadIdx.x / TX;
     const int x = blockIdx.x * TX + tx, y = blockIdx.y * TY + ty, z = blockIdx.z;
     double v[kPartialSlots] = {0, 0, 0, 0, 0};
     if (x < g.nx && y < g.ny) {
         const int n = x + g.px * (y + g.ny * z);
-        C rho, ga[3] = {C(0), C(0), C(0)};
-        if (MASK && mask[n]) {
+        const uint32_t lm = MASK ? links[n] : 0u;
+        C rho, u[3] = {C(0), C(0), C(0)};
+        if (MASK && link_solid(lm)) {
             rho = wall_density(p, n);
         } else {
             Nbr<D> nb(g, x, y, z);
             C h[Lat<D>::Q];
-            gather<D, S, C, MASK>(A, g.qs, mask, nb, n, h, p.link_q);
+            gather_links<D, S, C, MASK>(A, g.qs, lm, nb, n, h, p.link_q);
             C sum, j[3];
             moments_of<D, C>(h, sum, j);
             rho = p.rho_ref + sum;
             const C rinv = rcp(rho);
 #pragma unroll
-            for (int a = 0; a < D; ++a) {
-                const C ua = j[a] * rinv;
-                ga[a] = rho * ua * ua * ua;
-            }
+            for (int a = 0; a < D; ++a) u[a] = j[a] * rinv;
             v[0] = double(rho);
             v[1] = double(j[0]);
             v[2] = double(j[1]);
             v[3] = D == 3 ? double(j[2]) : 0.0;
             v[4] = p.eos.in_domain(rho) ? 0.0 : 1.0;
         }
-        rho_out[n] = rho;
+        if (rho_out) rho_out[n] = rho;
+        if (gf)
 #pragma unroll
-        for (int a = 0; a < D; ++a) gf[(long long)a * g.N + n] = ga[a];
+            for (int a = 0; a < D; ++a) gf[(long long)a * g.N + n] = rho * u[a] * u[a] * u[a];
+        const int un = x + g.nx * (y + g.ny * z);
+        if (out_rho) out_rho[un] = double(rho);
+        if (out_U)
+#pragma unroll
+            for (int a = 0; a < D; ++a) out_U[(long long)a * g.nx * g.ny * g.nz + un] = double(u[a]);
     }
     const int blk = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
     block_sum5(v, partials + (long long)blk * kPartialSlots);
+}
+
+// Solid-neighbour bits, one word per node (bit i: the source node n - c_i is solid; bit LINK_SELF: n is)
+template <int D>
+__global__ __launch_bounds__(256) void k_links(const uint8_t *__restrict__ mask, uint32_t *__restrict__ links, Geom g) {
+    const int n = blockIdx.x * 256 + threadIdx.x;
+    if (n >= g.N) return;
+    const int x = n % g.px, y = (n / g.px) % g.ny, z = n / (g.px * g.ny);
+    if (x >= g.nx) {   // row padding
+        links[n] = 0u;
+        return;
+    }
+    const Nbr<D> nb(g, x, y, z);
+    uint32_t b = mask[n] ? (1u << LINK_SELF) : 0u;
+    static_for<1, Lat<D>::Q>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        if (mask[nb.at(-Lat<D>::c(i, 0), -Lat<D>::c(i, 1), -Lat<D>::c(i, 2))]) b |= 1u << i;
+    });
+    links[n] = b;
 }
 
 // ------------------------------------------------------------------ pass 2
@@ -107,10 +136,10 @@ template <int D, int TYT = TY> struct Tile {
     static constexpr int LS = LX * LY * LZ;
 };
 
-enum { MODE_STEP = 0, MODE_OUT = 1, MODE_INIT = 2, MODE_PT = 3, MODE_SINGLE = 4 };
+enum { MODE_STEP = 0, MODE_VEL = 1, MODE_INIT = 2, MODE_PT = 3, MODE_SINGLE = 4 };
 
 // MODE_STEP: one collide-stream step A -> B.
-// MODE_OUT:  rho and U = u + S/(2 rho) of the state in A, FP64, into out_rho / out_U.
+// MODE_VEL:  U = u + S/(2 rho) in FP64 (user layout), in place of the bare u in out_U (D2Q9).
 // MODE_INIT: equilibrium of the density in rho_f and the flow velocity U0 (= out_U, may be
 //            NULL): bare u = U0 - S/(2 rho), written into B in pull layout.
 // MODE_PT:   discrete pressure tensor of the state in A (Appendix E) into out_U, FP64
@@ -123,9 +152,10 @@ enum { MODE_STEP = 0, MODE_OUT = 1, MODE_INIT = 2, MODE_PT = 3, MODE_SINGLE = 4 
 //            the moment pass computes them, instead of reading the moment pass's fields.
 template <int D, class S, class C, bool MASK, int MODE>
 __global__ __launch_bounds__(MODE == MODE_SINGLE ? TX * kSingleTY : TX * TY) void k_collide(
-    const S *__restrict__ A, S *__restrict__ B, Geom g, const uint8_t *__restrict__ mask, Params<C> p,
-    const C *__restrict__ rho_f, const C *__restrict__ gf, double *__restrict__ out_rho, double *__restrict__ out_U) {
-    constexpr bool OUT = MODE == MODE_OUT;
+    const S *__restrict__ A, S *__restrict__ B, Geom g, const uint8_t *__restrict__ mask,
+    const uint32_t *__restrict__ links, Params<C> p, const C *__restrict__ rho_f, const C *__restrict__ gf,
+    double *__restrict__ out_U) {
+    // MODE_INIT has the mask, the others the solid-neighbour bits
     constexpr bool SINGLE = MODE == MODE_SINGLE;
     static_assert(!SINGLE || D == 2, "single-pass mode: D2Q9");
     constexpr int TYK = SINGLE ? kSingleTY : TY, NTH = TX * TYK;
@@ -173,15 +203,16 @@ __global__ __launch_bounds__(MODE == MODE_SINGLE ? TX * kSingleTY : TX * TY) voi
         const int ox = wrapi(x0 + tx, g.nx), oy = wrapi(y0 + ty, g.ny);
         const int hx = wrapi(x0 - HALO + lx, g.nx), hy = wrapi(y0 - HALO + ly, g.ny);
         const int on = ox + g.px * oy, hn = hx + g.px * hy;
-        const bool osolid = MASK && mask[on], hsolid = MASK && has_halo && mask[hn];
+        const uint32_t olm = MASK ? links[on] : 0u, hlm = MASK && has_halo ? links[hn] : 0u;
+        const bool osolid = link_solid(olm), hsolid = link_solid(hlm);
         C hh[Lat<D>::Q];
         if (!osolid) {
             Nbr<D> nb(g, ox, oy, 0);
-            gather<D, S, C, MASK>(A, g.qs, mask, nb, on, h_own, p.link_q);
+            gather_links<D, S, C, MASK>(A, g.qs, olm, nb, on, h_own, p.link_q);
         }
         if (has_halo && !hsolid) {
             Nbr<D> nb(g, hx, hy, 0);
-            gather<D, S, C, MASK>(A, g.qs, mask, nb, hn, hh, p.link_q);
+            gather_links<D, S, C, MASK>(A, g.qs, hlm, nb, hn, hh, p.link_q);
         }
         auto finish = [&](int e, int gn, bool solid, const C (&h)[Lat<D>::Q]) __attribute__((always_inline)) {
             C r, ga[2] = {C(0), C(0)};
@@ -224,11 +255,8 @@ __global__ __launch_bounds__(MODE == MODE_SINGLE ? TX * kSingleTY : TX * TY) voi
         const int z = z0 + zz;
         if (z >= g.nz) break;
         const int n = x + g.px * (y + g.ny * z);
-        if (MASK && mask[n]) {
-            if constexpr (OUT) {
-                out_rho[n] = double(wall_density(p, n));
-                for (int a = 0; a < D; ++a) out_U[(long long)a * g.N + n] = 0.0;
-            }
+        const uint32_t lm = MASK && MODE != MODE_INIT ? links[n] : 0u;
+        if (MASK && (MODE == MODE_INIT ? mask[n] != 0 : link_solid(lm))) {
             if constexpr (MODE == MODE_PT)
                 for (int k = 0; k < D * (D + 1) / 2; ++k) out_U[(long long)k * g.N + n] = 0.0;
             continue;
@@ -237,7 +265,7 @@ __global__ __launch_bounds__(MODE == MODE_SINGLE ? TX * kSingleTY : TX * TY) voi
         if constexpr (MODE == MODE_PT) {
             Nbr<D> nb(g, x, y, z);
             C h[Lat<D>::Q];
-            gather<D, S, C, MASK>(A, g.qs, mask, nb, n, h, p.link_q);
+            gather_links<D, S, C, MASK>(A, g.qs, lm, nb, n, h, p.link_q);
             constexpr int NC = D * (D + 1) / 2;
             constexpr int ca[6] = {0, 1, D == 3 ? 2 : 0, 0, 0, 1}, cb[6] = {0, 1, D == 3 ? 2 : 1, 1, 2, 2};
             C flux[NC], ringA[NC], ringB[NC], across[NC], cap1[NC], cap2[NC], capx[NC];
@@ -302,6 +330,16 @@ __global__ __launch_bounds__(MODE == MODE_SINGLE ? TX * kSingleTY : TX * TY) voi
 #pragma unroll
         for (int a = 0; a < D; ++a) Sf[a] = rho * p.accel[a] - (C(2) * spc * Fp[a] + rho * Fc[a]);   // S = -F + rho g
 
+        if constexpr (MODE == MODE_VEL) {
+            const int un = x + g.nx * (y + g.ny * z);
+            const C half = C(0.5) * rcp(rho);
+#pragma unroll
+            for (int a = 0; a < D; ++a) {
+                double *U = out_U + (long long)a * g.nx * g.ny * g.nz + un;
+                *U = double(C(*U) + Sf[a] * half);
+            }
+            continue;
+        }
         Nbr<D> nb(g, x, y, z);
         C h[Lat<D>::Q];
         if constexpr (MODE == MODE_INIT) {
@@ -334,7 +372,7 @@ __global__ __launch_bounds__(MODE == MODE_SINGLE ? TX * kSingleTY : TX * TY) voi
 #pragma unroll
             for (int i = 0; i < Lat<D>::Q; ++i) h[i] = h_own[i];
         } else {
-            gather<D, S, C, MASK>(A, g.qs, mask, nb, n, h, p.link_q);
+            gather_links<D, S, C, MASK>(A, g.qs, lm, nb, n, h, p.link_q);
         }
         C drho, j[3];
         moments_of<D, C>(h, drho, j);
@@ -355,18 +393,101 @@ __global__ __launch_bounds__(MODE == MODE_SINGLE ? TX * kSingleTY : TX * TY) voi
             if constexpr (D == 3)
                 Phi[2] = cf * (gf[2LL * g.N + nb.at(0, 0, 1)] - gf[2LL * g.N + nb.at(0, 0, -1)]);
         }
-        if constexpr (OUT) {
-            out_rho[n] = double(rho);
+        collide<D, C>(h, rho, drho, u, Sf, Phi, omega);
+        static_for<0, Lat<D>::Q>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            st_nt_at(B + i * g.qs, (unsigned)n, S(h[i]));
+        });
+        }
+    }
+}
+
+// ------------------------------------------------------------------ velocity (D3Q27)
+// U = u + S/(2 rho) in place of the bare u in U (FP64, user layout), from the density field. One
+// workgroup marches a TX x TY column of nodes through tz planes with rho and s psi of the last
+// planes in an LDS ring: each plane's 68 x 8 densities are read and turned into s psi once
+// (2.1 per node; the 64 x 4 x 2 tile of k_collide takes 6.4, whose square roots and divisions
+// bound it). Plane z + 3 is loaded before plane z's stencil and stored behind it; with six slots
+// one barrier per plane is enough. Bound by the 104 LDS reads per node, then by HBM (56 bytes
+// per node): 256^3 FP32 0.215 ms, FP64 0.39 ms, 512x256x256 FP32 with pillars 0.48 ms, against
+// 0.59, 1.21 and 4.69 ms for an output pass that gathered the populations once more.
+template <class C, bool MASK>
+__global__ __launch_bounds__(TX *TY) void k_velocity3(Geom g, const uint32_t *__restrict__ links, Params<C> p,
+                                                      const C *__restrict__ rho_f, double *__restrict__ U, int tz) {
+    constexpr int LX = TX + 2 * HALO, LY = TY + 2 * HALO, LP = LX * LY, RING = 6, NTH = TX * TY;
+    constexpr int PER = (LP + NTH - 1) / NTH;   // staged entries per thread and plane
+    __shared__ C s_rho[RING * LP];
+    __shared__ C s_psi[RING * LP];
+    const int t = threadIdx.x, tx = t & (TX - 1), ty = t / TX;
+    const int x0 = blockIdx.x * TX, y0 = blockIdx.y * TY, z0 = blockIdx.z * tz, nzi = min(tz, g.nz - z0);
+    const int x = x0 + tx, y = y0 + ty, nxy = g.px * g.ny;
+    const bool own = x < g.nx && y < g.ny;
+    int at[PER];
 #pragma unroll
-            for (int a = 0; a < D; ++a) out_U[(long long)a * g.N + n] = double(u[a] + Sf[a] * (C(0.5) * rinv));
-        } else {
-            collide<D, C>(h, rho, drho, u, Sf, Phi, omega);
-            static_for<0, Lat<D>::Q>([&](auto I) {
+    for (int m = 0; m < PER; ++m) {
+        const int e = t + m * NTH;
+        at[m] = e < LP ? wrapi(x0 - HALO + e % LX, g.nx) + g.px * wrapi(y0 - HALO + e / LX, g.ny) : 0;
+    }
+    auto load = [&](int j, C (&r)[PER]) __attribute__((always_inline)) {   // plane z0 + j
+        const C *plane = rho_f + (long long)nxy * wrapi(z0 + j, g.nz);
+#pragma unroll
+        for (int m = 0; m < PER; ++m) r[m] = plane[at[m]];
+    };
+    auto stage = [&](int j, const C (&r)[PER]) __attribute__((always_inline)) {
+        const int slot = (j + 2) % RING * LP;
+#pragma unroll
+        for (int m = 0; m < PER; ++m) {
+            const int e = t + m * NTH;
+            if (e >= LP) break;
+            s_rho[slot + e] = r[m];
+            s_psi[slot + e] = signed_psi(p.eos, r[m]);
+        }
+    };
+    C r[PER];
+#pragma unroll 1
+    for (int j = -2; j <= 2; ++j) {
+        load(j, r);
+        stage(j, r);
+    }
+    __syncthreads();
+    const int e0 = (ty + HALO) * LX + tx + HALO;
+    const long long Nu = (long long)g.nx * g.ny * g.nz;
+#pragma unroll 1
+    for (int k = 0; k < nzi; ++k) {
+        const int z = z0 + k;
+        if (k + 1 < nzi) load(k + 3, r);
+        const bool act = own && !(MASK && link_solid(links[x + g.px * (y + g.ny * z)]));
+        if (act) {
+            double *u = U + (x + (long long)g.nx * (y + (long long)g.ny * z));
+            const double ub[3] = {u[0], u[Nu], u[2 * Nu]};
+            int base[5];
+#pragma unroll
+            for (int d = 0; d < 5; ++d) base[d] = (k + d) % RING * LP + e0;
+            const C rho = s_rho[base[2]], spc = s_psi[base[2]];
+            C Fp[3] = {C(0), C(0), C(0)}, Fc[3] = {C(0), C(0), C(0)};
+            static_for<1, 27>([&](auto I) {
                 constexpr int i = decltype(I)::value;
-                st_nt_at(B + i * g.qs, (unsigned)n, S(h[i]));
+                constexpr int cx = Lat<3>::c(i, 0), cy = Lat<3>::c(i, 1), cz = Lat<3>::c(i, 2);
+                constexpr int o1 = cy * LX + cx, cls = cx * cx + cy * cy + cz * cz - 1;
+                const int r1 = base[2 + cz] + o1, r2 = base[2 + 2 * cz] + 2 * o1;
+                const C tp = p.gw[cls][0] * fabs(s_psi[r1]) + p.gw[cls][1] * fabs(s_psi[r2]);
+                const C tc = p.gw[cls][2] * s_rho[r1] + p.gw[cls][3] * s_rho[r2];
+                static_for<0, 3>([&](auto A_) {
+                    constexpr int a = decltype(A_)::value;
+                    constexpr int ca = Lat<3>::c(i, a);
+                    if constexpr (ca == 1) { Fp[a] += tp; Fc[a] += tc; }
+                    if constexpr (ca == -1) { Fp[a] -= tp; Fc[a] -= tc; }
+                });
             });
+            const C half = C(0.5) * rcp(rho);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const C S = rho * p.accel[a] - (C(2) * spc * Fp[a] + rho * Fc[a]);
+                u[a * Nu] = double(C(ub[a]) + S * half);
+            }
         }
-        }
+        if (k + 1 < nzi) stage(k + 3, r);
+        __syncthreads();
     }
 }
 
@@ -497,40 +618,53 @@ template <int D, class S, class C, bool MASK> struct Launch {
         hipLaunchKernelGGL((k_prep_rho<C, MASK>), dim3((g.N + 255) / 256), dim3(256), 0, s, (C *)rho, rho0, mask,
                            p, g.N);
         hipLaunchKernelGGL((k_collide<D, S, C, MASK, MODE_INIT>), collide_grid(g), dim3(256), 0, s,
-                           (const S *)nullptr, (S *)A, g, mask, p, (const C *)rho, (const C *)nullptr,
-                           (double *)nullptr, (double *)U0);
+                           (const S *)nullptr, (S *)A, g, mask, nullptr, p, (const C *)rho, (const C *)nullptr,
+                           (double *)U0);
         if constexpr (MASK)
             if (p.link_q)
                 hipLaunchKernelGGL((k_wall_init<D, S, C>), dim3((g.N + 255) / 256), dim3(256), 0, s, (S *)A, g, mask,
                                    p.link_q);
     }
-    static void moments(hipStream_t s, const void *A, const Geom &g, const uint8_t *mask, const void *prm, void *rho,
-                        void *gfl, double *partials) {
-        hipLaunchKernelGGL((k_moments<D, S, C, MASK>), moment_grid(D, g), dim3(256), 0, s, (const S *)A, g, mask,
-                           *(const Params<C> *)prm, (C *)rho, (C *)gfl, partials);
+    static void make_links(hipStream_t s, const uint8_t *mask, uint32_t *links, const Geom &g) {
+        hipLaunchKernelGGL(k_links<D>, dim3((g.N + 255) / 256), dim3(256), 0, s, mask, links, g);
     }
-    static void collide(hipStream_t s, const void *A, void *B, const Geom &g, const uint8_t *mask, const void *prm,
+    static void moments(hipStream_t s, const void *A, const Geom &g, const uint32_t *links, const void *prm, void *rho,
+                        void *gfl, double *orho, double *oU, double *partials) {
+        hipLaunchKernelGGL((k_moments<D, S, C, MASK>), moment_grid(D, g), dim3(256), 0, s, (const S *)A, g, links,
+                           *(const Params<C> *)prm, (C *)rho, (C *)gfl, orho, oU, partials);
+    }
+    static void collide(hipStream_t s, const void *A, void *B, const Geom &g, const uint32_t *links, const void *prm,
                         const void *rho, const void *gfl) {
         hipLaunchKernelGGL((k_collide<D, S, C, MASK, MODE_STEP>), collide_grid(g), dim3(256), 0, s, (const S *)A, (S *)B, g,
-                           mask, *(const Params<C> *)prm, (const C *)rho, (const C *)gfl, nullptr, nullptr);
+                           nullptr, links, *(const Params<C> *)prm, (const C *)rho, (const C *)gfl, nullptr);
     }
-    static void single(hipStream_t s, const void *A, void *B, const Geom &g, const uint8_t *mask, const void *prm) {
+    static void single(hipStream_t s, const void *A, void *B, const Geom &g, const uint32_t *links, const void *prm) {
         if constexpr (D == 2)
             hipLaunchKernelGGL((k_collide<D, S, C, MASK, MODE_SINGLE>), dim3(single_blocks(g)),
-                               dim3(TX * kSingleTY), 0, s,
-                               (const S *)A, (S *)B, g, mask, *(const Params<C> *)prm, (const C *)nullptr,
-                               (const C *)nullptr, nullptr, nullptr);
+                               dim3(TX * kSingleTY), 0, s, (const S *)A, (S *)B, g, nullptr, links,
+                               *(const Params<C> *)prm, (const C *)nullptr, (const C *)nullptr, nullptr);
     }
-    static void pressure(hipStream_t s, const void *A, const Geom &g, const uint8_t *mask, const void *prm,
+    static void pressure(hipStream_t s, const void *A, const Geom &g, const uint32_t *links, const void *prm,
                          const void *rho, double *out) {
         hipLaunchKernelGGL((k_collide<D, S, C, MASK, MODE_PT>), collide_grid(g), dim3(256), 0, s, (const S *)A,
-                           (S *)nullptr, g, mask, *(const Params<C> *)prm, (const C *)rho, (const C *)nullptr, nullptr,
+                           (S *)nullptr, g, nullptr, links, *(const Params<C> *)prm, (const C *)rho, (const C *)nullptr,
                            out);
     }
-    static void output(hipStream_t s, const void *A, const Geom &g, const uint8_t *mask, const void *prm,
-                       const void *rho, const void *gfl, double *orho, double *oU) {
-        hipLaunchKernelGGL((k_collide<D, S, C, MASK, MODE_OUT>), collide_grid(g), dim3(256), 0, s, (const S *)A,
-                           (S *)nullptr, g, mask, *(const Params<C> *)prm, (const C *)rho, (const C *)gfl, orho, oU);
+    static void velocity(hipStream_t s, const Geom &g, const uint32_t *links, const void *prm, const void *rho,
+                         double *oU) {
+        if constexpr (D == 3) {
+            // planes per workgroup: long marches (each re-stages four planes), but about four
+            // workgroups per CU while chunks of four planes or more give them
+            const long long cols = (long long)((g.nx + TX - 1) / TX) * ((g.ny + TY - 1) / TY);
+            const int tz = (int)std::min<long long>(32, std::max<long long>(4, cols * g.nz / 1024));
+            hipLaunchKernelGGL((k_velocity3<C, MASK>),
+                               dim3((g.nx + TX - 1) / TX, (g.ny + TY - 1) / TY, (g.nz + tz - 1) / tz), dim3(TX * TY), 0, s, g,
+                               links, *(const Params<C> *)prm, (const C *)rho, oU, tz);
+        } else {
+            hipLaunchKernelGGL((k_collide<D, S, C, MASK, MODE_VEL>), collide_grid(g), dim3(256), 0, s, (const S *)nullptr,
+                               (S *)nullptr, g, nullptr, links, *(const Params<C> *)prm, (const C *)rho,
+                               (const C *)nullptr, oU);
+        }
     }
     static KernelSet set() {
         KernelSet k;
@@ -539,7 +673,8 @@ template <int D, class S, class C, bool MASK> struct Launch {
         k.moments = moments;
         k.collide = collide;
         k.single = D == 2 ? single : nullptr;
-        k.output = output;
+        k.links = make_links;
+        k.velocity = velocity;
         k.pressure = pressure;
         k.moment_blocks = 0;
         return k;

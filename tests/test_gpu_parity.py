@@ -524,6 +524,22 @@ def test_fused_plane_run_across_the_periodic_boundary_matches_two_pass(solid_pla
         assert max_rel(r, two[0]) < tol and np.abs(u - two[1]).max() < utol
 
 
+@pytest.mark.parametrize("masked", [False, True])
+@pytest.mark.parametrize("dims", [(64, 4, 4), (66, 5, 9), (130, 61, 37), (130, 61, 1)])
+def test_output_fields_at_tile_and_chunk_edges_match_the_oracle(dims, masked):
+    # density and velocity of a moving state: one tile, ragged tiles, padded rows (66, 130), and
+    # z-chunks of the velocity pass that do not divide nz; FP64, so within the parity bound 1e-10
+    D = 2 if dims[2] == 1 else 3
+    N = dims[0] * dims[1] * dims[2]
+    mask = L.random_mask(*dims, 0.1, 11) if masked else None
+    case = Case(D, *dims, a=0.02, T_reduced=0.8, rho_wall=2.0, mask=mask)
+    rho0, u0 = L.random_state(N, D, 1.0, 1.3, 0.02, 5)
+    for steps in (0, 2):
+        r_o, U_o, _ = run_oracle(case, rho0, u0, steps)
+        r_g, U_g, _ = run_gpu(case, rho0, u0, steps)
+        assert max_rel(r_g, r_o) < 1e-10 and np.abs(U_g - U_o).max() < 1e-10
+
+
 # ---------------------------------------------------------------- batched sweep
 def _sweep_cases(n, steps_len_lo=32, steps_len_hi=96):
     """A reduced temperature sweep: D2Q9 4 x L flat interfaces, FP64 from T/Tc >= 0.95."""
