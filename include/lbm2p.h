@@ -115,8 +115,8 @@ typedef struct {
                                contexts take the single-pass interpolating kernel on
                                planes within three planes of a solid node (the two-pass
                                step when the single-pass step is not available for the
-                               grid); D2Q9 takes it in its single-pass step (and in the
-                               two-pass step under LBM2P_TWO_PASS=1); lbm_batch_create
+                               grid); D2Q9 takes it in its tiles (and in the two-pass
+                               step under LBM2P_TWO_PASS=1); lbm_batch_create
                                rejects it. Copied at create */
     int force_model;        /* LBM_FORCE_* (0: eq Kforce_final) */
     double force_g[4];      /* coefficients for LBM_FORCE_DUAL_RANGE ([0] = G1) and
@@ -143,15 +143,15 @@ int lbm_init_fields(lbm_ctx *c, const double *rho, const double *u);
 /* Advances n time steps of eq LBGK (stream-collide with the Korteweg force and
  * halfway, or with link_q interpolated, bounce-back at solid nodes). Runs the FP64 watchdog as selected by
  * check_every; returns LBM_E_DIVERGED / LBM_E_DOMAIN when it trips. When no
- * check runs, the call only enqueues work on the context stream. A D2Q9 step is one
- * kernel; a D3Q27 step is the fused z-march, or on grids too small for it the moment
- * pass and then the collide (LBM2P_TWO_PASS=1 takes the latter for both lattices;
- * in D2Q9 the two agree to rounding). Contexts off the fused D3Q27 step
- * capture 32 steps into a HIP graph on the first call with at least 32 steps between
- * two checks. Such runs then replay that graph on the context stream, with results
- * identical bit for bit; the capture uses the context's own stream. Steps are
- * launched one by one when the context stream is itself being captured, or when the
- * environment sets LBM2P_GRAPH=0. */
+ * check runs, the call only enqueues work on the context stream. D2Q9 advances tiles by one
+ * to three steps per launch; a D3Q27 step is the fused z-march, or on grids too small for it the
+ * moment pass and then the collide (LBM2P_TWO_PASS=1 takes the latter for both lattices; in
+ * D2Q9 the two agree to rounding). Results do not depend, bit for bit, on how a run is cut into
+ * calls. Contexts off the fused D3Q27 step capture about 32 steps into a HIP graph on the first
+ * call with at least as many between two checks. Such runs then replay that graph on the
+ * context stream, with results identical bit for bit; the capture uses the context's own stream.
+ * Launches are made one by one when the context stream is itself being captured, or when the
+ * environment sets LBM2P_GRAPH=0. The two lattices swap roles once per step either way. */
 int lbm_step(lbm_ctx *c, int64_t n);
 
 /* Density and velocity of the current state. rho: host [N] (nullable); U: host

@@ -1,0 +1,382 @@
+// d2q9_kernels.hip -- the D2Q9 stream-collide step, one to kMaxTileSteps steps per launch (gfx950).
+//
+// A workgroup advances a tile of tx x ty nodes by nsteps steps in LDS. Step s (of nsteps, r =
+// nsteps - 1 - s steps still to come) needs the densities of the tile widened by m = 2 + 3 r
+// nodes on every side (one node for the pull of the next step, two for the ring stencils of the
+// nodes it pulls from) and collides the tile widened by m - 2:
+//   fields:  every node of the widened tile pulls its populations, from the lattice in step 0 and
+//            from LDS afterwards (halfway or interpolated bounce-back at solid links), and leaves
+//            rho, s psi and g = rho u^3 in LDS; the populations stay in registers;
+//   collide: two-ring force (eq Kforce_final) and correction (eq correction) from LDS, LBGK
+//            update (eqs LBMeq, LBMstar, LBGK) in registers, post-collision populations back to
+//            LDS, or in the last step to the other lattice.
+// Nodes outside the tile are recomputed by the neighbouring workgroups. One loop body serves
+// every step of every tile, so the state does not depend on the tile or on how a run is cut
+// into launches, bit for bit.
+#include <hip/hip_runtime.h>
+#include <math.h>
+
+#include <algorithm>
+
+#include "d2q9.hpp"
+#include "lattice.hpp"
+#include "step_common.hpp"
+
+namespace lbm {
+
+namespace {
+
+constexpr int kXcds = 8;         // MI355X: workgroups are dealt to 8 XCDs in turn
+constexpr int kXcdChunk = 128;   // consecutive tiles per XCD chunk, at most
+
+// node e of a region of width w: row e / w by a multiplication, exact while e w < 2^20 with
+// inv = 2^20 / w + 1
+__device__ __forceinline__ int row_of(int e, unsigned inv) { return (int)(((unsigned)e * inv) >> 20); }
+
+// A uniform value kept in a vector register. The step's constants take more scalar registers
+// than there are beside the addresses; spilled, each use costs two lane reads.
+__device__ __forceinline__ float in_vgpr(float v) { asm volatile("" : "+v"(v)); return v; }
+__device__ __forceinline__ double in_vgpr(double v) { asm volatile("" : "+v"(v)); return v; }
+// An opaque zero: an address with it added is computed where it is used, and not held in scalar
+// registers over the step loop.
+__device__ __forceinline__ long long here() {
+    long long z = 0;
+    asm volatile("" : "+s"(z));
+    return z;
+}
+
+// wrapi with one addition for all but the smallest grids
+__device__ __forceinline__ int wrap1(int v, int n) {
+    v = v < 0 ? v + n : (v >= n ? v - n : v);
+    return wrapi(v, n);
+}
+
+template <class C> struct alignas(2 * sizeof(C)) Pair { C rho, psi; };   // psi signed
+
+// quotient of n by a uniform d with inv = min(ceil(2^32 / d), 2^32 - 1): the estimate is off by one at most
+__device__ __forceinline__ int quotient(int n, int d, unsigned inv, int &rem) {
+    int q = (int)__umulhi((unsigned)n, inv);
+    rem = n - q * d;
+    if (rem < 0) { --q; rem += d; }
+    if (rem >= d) { ++q; rem -= d; }
+    return q;
+}
+
+// tile of this workgroup (false: padding). The hardware deals workgroups to the XCDs in turn; the
+// tiles, in row-major order, go to them in chunks of equal numbers of consecutive tiles, so that
+// neighbouring tiles mostly share an XCD and read each other's halo from its L2, and each XCD gets
+// as many (chunks of 128 with a remainder left some XCDs twice the work: 1000x900 FP32 22.8
+// us a step, in equal shares 16.8).
+__device__ __forceinline__ bool tile_of_block(const D2Tiles &tl, int &ix, int &iy) {
+    int k;
+    const int c = quotient((int)(blockIdx.x / kXcds), tl.chunk, tl.inv_chunk, k);
+    const int tile = (c * kXcds + (int)(blockIdx.x % kXcds)) * tl.chunk + k;
+    if (tile >= tl.ntx * tl.nty) return false;
+    iy = quotient(tile, tl.ntx, tl.inv_ntx, ix);
+    return true;
+}
+
+// Collides one node: force and correction from the LDS fields around it (rp, gx, gy point at the
+// node's entries, rows of W), the populations in h updated in place. gw: ring factors of psi
+// (axis, diagonal) and rho of the first ring, then of the second.
+template <class C>
+__device__ __forceinline__ void update_node(const Params<C> &p, const C (&gw)[8], const Pair<C> *rp, const C *gx, const C *gy,
+                                            int W, C rho_ref, C accx, C accy, C drho, C rinv, C spsi, const C (&j)[2],
+                                            C (&h)[9]) {
+    const C rho = rho_ref + drho;
+    const C accel[2] = {accx, accy};
+    C S2[2];
+    source_plane<C>(gw, rho, spsi, accel, [&](int k, int x, int y) __attribute__((always_inline)) { return rp[k * (x + y * W)]; }, S2);
+    const C omega = omega_of(p, rho), cf = (C(1) - C(0.5) * omega) * C(0.5);
+    const C Phi[2] = {cf * (gx[1] - gx[-1]), cf * (gy[W] - gy[-W])};
+    update_plane<C>(h, rho, drho, rinv, j, S2, Phi, omega);
+}
+
+// Bound by the vector instructions of the nodes and their halo, with the launch itself on small
+// grids: per launch of two steps of 32 x 32 tiles (512^2 FP32, 10 us) 1 us prologue, 2.5 us pulls,
+// 2.5 us first step, 2.5 us second step, 2 us gap to the next launch. What a step costs is its
+// instruction count, so the force takes differences before factors, the update gathers its
+// terms by axis (collide_plane), and constants sit in vector registers. Holding a frame of
+// populations in LDS, loaded with 16-byte copies, was slower (5.5 against 5.1 us a step).
+template <class S, class C, bool MASK, int NT, int NPT>
+__global__ __launch_bounds__(NT) void k_d2q9(const S *__restrict__ A, S *__restrict__ B, Geom g,
+                                             const uint32_t *__restrict__ links, Params<C> p, D2Tiles tl) {
+    constexpr int Q = 9, F0 = d2_fields(NT, NPT), P0 = d2_pops(NT, NPT);
+    extern __shared__ __align__(16) char lds[];
+    int ix, iy;
+    if (!tile_of_block(tl, ix, iy)) return;   // the padding of the last XCD's share (whole workgroup)
+    const int x0 = ix * tl.tx, y0 = iy * tl.ty;
+
+    const int t = threadIdx.x;
+    Pair<C> *const s_rp = (Pair<C> *)lds;
+    C *const s_gx = (C *)(s_rp + F0), *const s_gy = s_gx + F0;
+    S *const s_pop = (S *)(s_gy + F0);
+    int *const s_col = (int *)(s_pop + (tl.nsteps > 1 ? Q * P0 : 0));
+    // wrapped columns and row offsets of the first step's region and one node around it
+    const int m0 = 3 * tl.nsteps, W0 = tl.tx + 2 * m0, H0 = tl.ty + 2 * m0;
+    int *const s_row = s_col + W0;
+    for (int k = t; k < W0 + H0; k += NT) s_col[k] = k < W0 ? wrap1(x0 - m0 + k, g.nx) : g.px * wrap1(y0 - m0 + k - W0, g.ny);
+
+    const C gw[8] = {in_vgpr(p.gw[0][0]), in_vgpr(p.gw[1][0]), in_vgpr(p.gw[0][2]), in_vgpr(p.gw[1][2]),
+                     in_vgpr(p.gw[0][1]), in_vgpr(p.gw[1][1]), in_vgpr(p.gw[0][3]), in_vgpr(p.gw[1][3])};
+    const C rho_ref = in_vgpr(p.rho_ref), accx = in_vgpr(p.accel[0]), accy = in_vgpr(p.accel[1]);
+    // waves past a region's end skip (a scalar branch); the lanes of its last wave that are past
+    // it repeat its last node, so that little here is conditional per lane
+    const int w0 = __builtin_amdgcn_readfirstlane(t & ~63);
+    __syncthreads();
+
+    for (int st = 0; st < tl.nsteps; ++st) {
+        const int rem = tl.nsteps - 1 - st, m = 2 + 3 * rem;
+        const int W = tl.tx + 2 * m, H = tl.ty + 2 * m, F = W * H;
+        const unsigned inv = tl.inv[rem];
+        C h[NPT][Q];
+        C drho[NPT], jx[NPT], jy[NPT], rinv[NPT], spsi[NPT];
+        uint32_t lm[NPT];
+        // pulls of every node of this thread (a run-time first step, so that the compiler peels no
+        // copy of the body for it)
+        if (st == tl.first) {
+            const S *const Ah = A + here();
+#pragma unroll
+            for (int k = 0; k < NPT; ++k) {
+                if (w0 + k * NT >= F) break;
+                const int e = min(t + k * NT, F - 1), ry = row_of(e, inv), rx = e - ry * W;
+                const int xs[3] = {s_col[rx], s_col[rx + 1], s_col[rx + 2]};
+                const int ro[3] = {s_row[ry], s_row[ry + 1], s_row[ry + 2]};
+                const int pz[3] = {0, 0, 0};
+                const Nbr<2> nb(xs, ro, pz);
+                const int n = xs[1] + ro[1];
+                lm[k] = MASK ? links[n] : 0u;
+                gather_links<2, S, C, MASK>(Ah, g.qs, lm[k], nb, n, h[k], p.link_q);
+            }
+        } else {
+            const int Wp = W + 2;   // the region the previous step collided: one node wider on each side
+#pragma unroll
+            for (int k = 0; k < NPT; ++k) {
+                if (w0 + k * NT >= F) break;
+                const int e = min(t + k * NT, F - 1), ry = row_of(e, inv), rx = e - ry * W;
+                const int o = rx + 1 + (ry + 1) * Wp;
+                const int n = MASK ? s_col[rx + 1 + 3 * st] + s_row[ry + 1 + 3 * st] : 0;
+                lm[k] = MASK ? links[n] : 0u;
+                static_for<0, Q>([&](auto I) {
+                    constexpr int i = decltype(I)::value, cx = Lat<2>::c(i, 0), cy = Lat<2>::c(i, 1);
+                    const bool w = MASK && ((lm[k] >> i) & 1u);
+                    h[k][i] = C(s_pop[w ? opp<2>(i) * P0 + o : i * P0 + o - cx - cy * Wp]);
+                });
+                if (MASK && p.link_q && (lm[k] & ((1u << LINK_SELF) - 1u)))
+                    static_for<1, Q>([&](auto I) {   // interpolated bounce-back, as in gather_links
+                        constexpr int i = decltype(I)::value, q_ = opp<2>(i);
+                        constexpr int cx = Lat<2>::c(i, 0), cy = Lat<2>::c(i, 1);
+                        if ((lm[k] >> i) & 1u)
+                            h[k][i] = wall_mix<C>(ld_at(p.link_q + q_ * g.qs, (unsigned)n), h[k][i], (lm[k] >> q_) & 1u,
+                                                  C(s_pop[q_ * P0 + o + cx + cy * Wp]), C(s_pop[i * P0 + o]));
+                    });
+            }
+        }
+        // rho, s psi and g of every node
+#pragma unroll
+        for (int k = 0; k < NPT; ++k) {
+            if (w0 + k * NT >= F) break;
+            const int e = min(t + k * NT, F - 1);
+            C j[3];
+            moments_of<2, C>(h[k], drho[k], j);
+            C rho = rho_ref + drho[k];
+            jx[k] = j[0];
+            jy[k] = j[1];
+            rinv[k] = rcp(rho);
+            C ga[2];
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+                const C ua = j[a] * rinv[k];
+                ga[a] = rho * ua * ua * ua;
+            }
+            if (MASK && link_solid(lm[k])) {
+                rho = p.rho_w;
+                if (p.rho_wf) {
+                    const int ry = row_of(e, inv), rx = e - ry * W;
+                    rho = p.rho_wf[s_col[rx + 1 + 3 * st] + s_row[ry + 1 + 3 * st]];
+                }
+                ga[0] = ga[1] = C(0);
+            }
+            spsi[k] = signed_psi(p.eos, rho);
+            s_rp[e] = Pair<C>{rho, spsi[k]};
+            s_gx[e] = ga[0];
+            s_gy[e] = ga[1];
+        }
+        __syncthreads();
+        // force, correction, collision
+        const int Wc = W - 4;
+        S *const Bh = B + here();
+#pragma unroll
+        for (int k = 0; k < NPT; ++k) {
+            if (w0 + k * NT >= F) break;
+            const int e = min(t + k * NT, F - 1), ry = row_of(e, inv), rx = e - ry * W;
+            if ((unsigned)(rx - 2) < (unsigned)Wc && (unsigned)(ry - 2) < (unsigned)(H - 4) &&
+                !(MASK && link_solid(lm[k]))) {
+                const C j[2] = {jx[k], jy[k]};
+                update_node<C>(p, gw, s_rp + e, s_gx + e, s_gy + e, W, rho_ref, accx, accy, drho[k], rinv[k], spsi[k], j, h[k]);
+                if (rem) {
+                    const int o = rx - 2 + (ry - 2) * Wc;
+                    static_for<0, Q>([&](auto I) {
+                        constexpr int i = decltype(I)::value;
+                        s_pop[i * P0 + o] = S(h[k][i]);
+                    });
+                } else {
+                    const int x = x0 + rx - 2, y = y0 + ry - 2;
+                    if (x < g.nx && y < g.ny)
+                        static_for<0, Q>([&](auto I) {
+                            constexpr int i = decltype(I)::value;
+                            st_nt_at(Bh + i * g.qs, (unsigned)(x + g.px * y), S(h[k][i]));
+                        });
+                }
+            }
+        }
+        if (rem) __syncthreads();   // the next step pulls these populations and overwrites the fields
+    }
+}
+
+// One step per launch on a 64 x 8 tile, one thread per tile node, 304 of which also pull one node of
+// the two-node halo. Only the tile's own nodes are collided and kept in registers, and two
+// workgroups share a CU, so this moves a large FP64 grid faster than the tiles above, whose
+// recomputed halo costs more there than the launches and traffic they save: 2040x1900 FP64 121 us
+// a step, 4.6 TB/s of populations against 5.4 for a copy, and 126 in tiles.
+constexpr int SX = 64, SY = 8, SHALO = 2;
+template <class S, class C, bool MASK>
+__global__ __launch_bounds__(SX *SY) void k_d2q9_single(const S *__restrict__ A, S *__restrict__ B, Geom g,
+                                                        const uint32_t *__restrict__ links, Params<C> p, D2Tiles tl) {
+    constexpr int LX = SX + 2 * SHALO, LY = SY + 2 * SHALO, LS = LX * LY, NTH = SX * SY, NH = LS - NTH;
+    static_assert(NH <= NTH, "one halo node per thread at most");
+    __shared__ Pair<C> s_rp[LS];
+    __shared__ C s_gx[LS], s_gy[LS];
+    int ix, iy;
+    if (!tile_of_block(tl, ix, iy)) return;   // the padding of the last XCD's share (whole workgroup)
+    const int x0 = ix * SX, y0 = iy * SY;
+    // every thread its own tile node (wrapped past the grid's edge: those feed the stencils of the
+    // last columns and rows), and at most one halo node: rows 0, 1, LY-2, LY-1 of the staged
+    // tile, then columns 0, 1, LX-2, LX-1 of the rows between. Both nodes' pulls are issued
+    // before either is reduced.
+    const int t = threadIdx.x, tx = t & (SX - 1), ty = t / SX;
+    const bool has_halo = t < NH;
+    int lx = 0, ly = 0;
+    if (t < 4 * LX) {
+        const int r = t / LX;
+        lx = t % LX;
+        ly = r < 2 ? r : SY + r;
+    } else if (has_halo) {
+        const int q = t - 4 * LX, c4 = q % 4;
+        ly = 2 + q / 4;
+        lx = c4 < 2 ? c4 : SX + c4;
+    }
+    const int e = (ty + SHALO) * LX + tx + SHALO, e_halo = ly * LX + lx;
+    const int ox = wrap1(x0 + tx, g.nx), oy = wrap1(y0 + ty, g.ny);
+    const int hx = wrap1(x0 - SHALO + lx, g.nx), hy = wrap1(y0 - SHALO + ly, g.ny);
+    const int on = ox + g.px * oy, hn = hx + g.px * hy;
+    const uint32_t olm = MASK ? links[on] : 0u, hlm = MASK && has_halo ? links[hn] : 0u;
+    C h[9], hh[9];
+    if (!link_solid(olm)) gather_links<2, S, C, MASK>(A, g.qs, olm, Nbr<2>(g, ox, oy, 0), on, h, p.link_q);
+    if (has_halo && !link_solid(hlm)) gather_links<2, S, C, MASK>(A, g.qs, hlm, Nbr<2>(g, hx, hy, 0), hn, hh, p.link_q);
+    C drho = C(0), rinv = C(0), spsi = C(0), jj[2] = {C(0), C(0)};
+    auto stage = [&](int at, int n, uint32_t lm, const C (&hs)[9], bool own) __attribute__((always_inline)) {
+        C rho, ga[2] = {C(0), C(0)};
+        if (MASK && link_solid(lm)) {
+            rho = wall_density(p, n);
+        } else {
+            C sum, j[3];
+            moments_of<2, C>(hs, sum, j);
+            rho = p.rho_ref + sum;
+            const C ri = rcp(rho);
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+                const C ua = j[a] * ri;
+                ga[a] = rho * ua * ua * ua;
+            }
+            if (own) { drho = sum; rinv = ri; jj[0] = j[0]; jj[1] = j[1]; }
+        }
+        const C sp = signed_psi(p.eos, rho);
+        if (own) spsi = sp;
+        s_rp[at] = Pair<C>{rho, sp};
+        s_gx[at] = ga[0];
+        s_gy[at] = ga[1];
+    };
+    stage(e, on, olm, h, true);
+    if (has_halo) stage(e_halo, hn, hlm, hh, false);
+    __syncthreads();
+    const int x = x0 + tx, y = y0 + ty;
+    if (x >= g.nx || y >= g.ny || link_solid(olm)) return;
+    const C gw[8] = {p.gw[0][0], p.gw[1][0], p.gw[0][2], p.gw[1][2], p.gw[0][1], p.gw[1][1], p.gw[0][3], p.gw[1][3]};
+    update_node<C>(p, gw, s_rp + e, s_gx + e, s_gy + e, LX, p.rho_ref, p.accel[0], p.accel[1], drho, rinv, spsi, jj, h);
+    static_for<0, 9>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        st_nt_at(B + i * g.qs, (unsigned)(x + g.px * y), S(h[i]));
+    });
+}
+
+// workgroups of a launch: its tiles, padded to a whole number of chunks per XCD
+unsigned blocks(const D2Tiles &t) {
+    const int nt = t.ntx * t.nty, per = kXcds * t.chunk;
+    return (unsigned)((nt + per - 1) / per) * (unsigned)per;
+}
+
+// workgroup shapes: threads x nodes per thread (0: the single step)
+template <class S, class C, bool MASK, int NT, int NPT>
+void launch(hipStream_t s, const void *A, void *B, const Geom &g, const uint32_t *links, const void *prm,
+            const D2Tiles &t) {
+    hipLaunchKernelGGL((k_d2q9<S, C, MASK, NT, NPT>), dim3(blocks(t)), dim3(NT), t.lds, s,
+                       (const S *)A, (S *)B, g, links, *(const Params<C> *)prm, t);
+}
+
+template <class S, class C, bool MASK>
+void launch_single(hipStream_t s, const void *A, void *B, const Geom &g, const uint32_t *links, const void *prm,
+                   const D2Tiles &t) {
+    hipLaunchKernelGGL((k_d2q9_single<S, C, MASK>), dim3(blocks(t)), dim3(SX * SY), 0, s, (const S *)A, (S *)B, g, links,
+                       *(const Params<C> *)prm, t);
+}
+
+template <class S, class C, bool MASK>
+D2Launch pick(int threads, int per) {
+    switch (threads * 8 + per) {
+    case SX * SY * 8: return launch_single<S, C, MASK>;
+    case 256 * 8 + 1: return launch<S, C, MASK, 256, 1>;
+    case 512 * 8 + 2: return launch<S, C, MASK, 512, 2>;
+    case 512 * 8 + 3: return launch<S, C, MASK, 512, 3>;
+    case 1024 * 8 + 2: if constexpr (sizeof(C) == 4) return launch<S, C, MASK, 1024, 2>; else return nullptr;   // 128 registers
+    default: return nullptr;
+    }
+}
+
+}  // namespace
+
+D2Tiles d2_tiles(const Geom &g, bool fp64, const D2Shape &sh, int nsteps) {
+    D2Tiles t;
+    t.tx = sh.tx;
+    t.ty = sh.ty;
+    t.ntx = (g.nx + t.tx - 1) / t.tx;
+    t.nty = (g.ny + t.ty - 1) / t.ty;
+    t.nsteps = nsteps;
+    t.first = 0;
+    const int nt = t.ntx * t.nty, full = kXcds * kXcdChunk, rounds = (nt + full - 1) / full;
+    t.chunk = (nt + kXcds * rounds - 1) / (kXcds * rounds);
+    auto inverse = [](int d) { return (unsigned)std::min<unsigned long long>(((1ull << 32) + d - 1) / d, 0xFFFFFFFFull); };
+    t.inv_chunk = inverse(t.chunk);
+    t.inv_ntx = inverse(t.ntx);
+    const int m0 = 3 * nsteps;
+    t.lds = (size_t)(fp64 ? 8 : 4) * (4 * (size_t)d2_fields(sh.threads, sh.per) +
+                                      (nsteps > 1 ? 9 * (size_t)d2_pops(sh.threads, sh.per) : 0)) +
+            sizeof(int) * (size_t)(t.tx + t.ty + 4 * m0);
+    for (int r = 0; r < kMaxTileSteps; ++r) t.inv[r] = (1u << 20) / (unsigned)(t.tx + 2 * (2 + 3 * r)) + 1u;
+    return t;
+}
+
+bool d2_fits(bool fp64, const D2Shape &sh) {
+    if (sh.per == 0) return sh.threads == SX * SY && sh.tx == SX && sh.ty == SY && sh.steps == 1;
+    if (sh.steps < 1 || sh.steps > kMaxTileSteps || sh.tx < 1 || sh.ty < 1 || sh.tx > 192 || sh.ty > 192) return false;
+    const int m = 2 + 3 * (sh.steps - 1), w = sh.tx + 2 * m, h = sh.ty + 2 * m;
+    return w * h <= d2_fields(sh.threads, sh.per) && (sh.steps == 1 || (w - 4) * (h - 4) <= d2_pops(sh.threads, sh.per)) &&
+           d2_tiles(Geom{1, 1, 1, 1, 1, 1}, fp64, sh, sh.steps).lds <= 160 * 1024;
+}
+
+D2Launch d2_launcher(bool fp64, bool masked, const D2Shape &sh) {
+    if (fp64) return masked ? pick<double, double, true>(sh.threads, sh.per) : pick<double, double, false>(sh.threads, sh.per);
+    return masked ? pick<float, float, true>(sh.threads, sh.per) : pick<float, float, false>(sh.threads, sh.per);
+}
+
+}  // namespace lbm

@@ -60,9 +60,6 @@ struct KernelSet {
     // one collide-stream step A -> B (reads rho, g written by moments)
     void (*collide)(hipStream_t, const void *A, void *B, const Geom &, const uint32_t *links, const void *params,
                     const void *rho, const void *g);
-    // one collide-stream step A -> B in a single pass, rho and g from the tile's own pulls
-    // (D2Q9; nullptr for D3Q27)
-    void (*single)(hipStream_t, const void *A, void *B, const Geom &, const uint32_t *links, const void *params);
     // adds S/(2 rho) to the bare velocity that moments left in out_U (reads rho)
     void (*velocity)(hipStream_t, const Geom &, const uint32_t *links, const void *params, const void *rho,
                      double *out_U);

@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "../../include/lbm2p.h"
+#include "d2q9.hpp"
 #include "fused.hpp"
 #include "kernels.hpp"
 #include "runtime_common.hpp"
@@ -61,10 +62,13 @@ struct lbm_ctx {
     Params<double> pd{};
     Params<float> pf{};
     KernelSet ks{};
-    hipGraphExec_t gexec = nullptr;  // steps off the fused kernel: kGraphSteps captured once, replayed
+    hipGraphExec_t gexec = nullptr;  // steps off the fused kernel: graph_steps captured once, replayed
+    int graph_steps = 32;
     void *gA = nullptr;              // the lattice those captured steps start from
     bool use_graph = false;
-    bool single = false;             // D2Q9: single-pass step (ks.single) instead of moments + collide
+    D2Launch d2 = nullptr;           // D2Q9: steps in tiles instead of moments + collide
+    int tile_steps = 1;              // most steps per launch of those
+    D2Tiles tiles[kMaxTileSteps];    // launches of 1 .. tile_steps steps
     FusedLaunch fused = nullptr;     // single-pass step when available (D3Q27): the first segment's kernel
     std::vector<FusedSeg> segs;      // the launches of one fused step, over disjoint plane ranges
     bool initialized = false;
@@ -174,42 +178,53 @@ void fused_step(lbm_ctx *c) {
         sg.fn(c->stream, c->A, c->B, c->g, FusedMask{c->links, c->pflags, c->qlo}, params_ptr(c), sg.fg);
 }
 
-// the two-pass step, or the D2Q9 single pass, from lattice a into b on stream s
-void unfused_step(lbm_ctx *c, hipStream_t s, const void *a, void *b) {
-    if (c->single) {
-        c->ks.single(s, a, b, c->g, c->links, params_ptr(c));
+// k steps from lattice a into b on stream s: one launch of the D2Q9 tiles, or the two-pass step (k = 1)
+void unfused_steps(lbm_ctx *c, hipStream_t s, const void *a, void *b, int k) {
+    if (c->d2) {
+        c->d2(s, a, b, c->g, c->links, params_ptr(c), c->tiles[k - 1]);
     } else {
         c->ks.moments(s, a, c->g, c->links, params_ptr(c), c->rho, c->gfl, nullptr, nullptr, c->partials);
         c->ks.collide(s, a, b, c->g, c->links, params_ptr(c), c->rho, c->gfl);
     }
 }
 
-int one_step(lbm_ctx *c) {
-    ++c->steps;
+// Steps of the next launch when n remain. A launch swaps the lattices once whatever its steps,
+// and callers (and captured graphs) rely on the lattices swapping roles once per step, so
+// launches take odd numbers of steps, or tile_steps of them twice in a row when that is even.
+int next_launch(const lbm_ctx *c, int64_t n, bool second) {
+    const int most = c->tile_steps;
+    if (most % 2 == 0 && (second || n >= 2 * most)) return most;
+    const int odd = most % 2 ? most : most - 1;
+    return n >= odd ? odd : (int)(n - 1) / 2 * 2 + 1;
+}
+
+// one launch (a fused step: its launches) of k steps
+void step_once(lbm_ctx *c, int k) {
+    c->steps += k;
     if (c->fused) {
         fused_step(c);
         c->folded = c->fold;
     } else {
-        unfused_step(c, c->stream, c->A, c->B);
+        unfused_steps(c, c->stream, c->A, c->B, k);
     }
-    void *t = c->A; c->A = c->B; c->B = t;
-    return LBM_OK;
+    std::swap(c->A, c->B);
 }
 
-// Steps off the fused kernel (the D2Q9 single pass, the two-pass step) per captured graph.
-// Even, so that a replay leaves the two lattices in the roles it found them in; 32 steps
-// make the host's launch cost per step small next to a grid's own time down to a few
-// thousand nodes.
+// Steps off the fused kernel (D2Q9 tiles, the two-pass step) per captured graph: about this
+// many, in an even number of launches, so that a replay leaves the two lattices in the roles
+// it found them in; they make the host's launch cost per step small next to a grid's own
+// time down to a few thousand nodes.
 constexpr int kGraphSteps = 32;
 
-// Captures kGraphSteps steps from the current lattice on the context's own stream (never the
+// Captures graph_steps steps from the current lattice on the context's own stream (never the
 // caller's, which may itself be capturing). The graph holds kernels only.
 int capture_steps(lbm_ctx *c) {
     HIP_OR_FAIL(c, hipStreamSynchronize(c->own));   // once per context: nothing queued under the capture
     HIP_OR_FAIL(c, hipStreamBeginCapture(c->own, hipStreamCaptureModeThreadLocal));
     void *a = c->A, *b = c->B;
-    for (int s = 0; s < kGraphSteps; ++s) {
-        unfused_step(c, c->own, a, b);
+    for (int s = 0, k; s < c->graph_steps; s += k) {
+        k = c->tile_steps;
+        unfused_steps(c, c->own, a, b, k);
         std::swap(a, b);
     }
     const hipError_t le = hipGetLastError();
@@ -228,11 +243,11 @@ int capture_steps(lbm_ctx *c) {
 }
 
 // n steps with no check among them. Steps off the fused kernel replay the captured block
-// while at least kGraphSteps steps remain (after one plain step when the lattices are in the
-// other roles), unless the context's stream is being captured by the caller; the rest go one
-// by one.
+// while at least graph_steps steps remain (after one plain step when the lattices are in the
+// other roles), unless the context's stream is being captured by the caller; the rest go
+// launch by launch.
 int run_steps(lbm_ctx *c, int64_t n) {
-    if (c->use_graph && n >= kGraphSteps) {
+    if (c->use_graph && n >= c->graph_steps) {
         hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
         HIP_OR_FAIL(c, hipStreamIsCapturing(c->stream, &st));
         if (st == hipStreamCaptureStatusNone) {
@@ -241,16 +256,21 @@ int run_steps(lbm_ctx *c, int64_t n) {
                 if (rc) return rc;
             }
             if (c->A != c->gA) {
-                one_step(c);
+                step_once(c, 1);
                 --n;
             }
-            for (; n >= kGraphSteps; n -= kGraphSteps) {
+            for (; n >= c->graph_steps; n -= c->graph_steps) {
                 HIP_OR_FAIL(c, hipGraphLaunch(c->gexec, c->stream));
-                c->steps += kGraphSteps;
+                c->steps += c->graph_steps;
             }
         }
     }
-    for (; n > 0; --n) one_step(c);
+    for (bool second = false; n > 0;) {
+        const int k = next_launch(c, n, second);
+        step_once(c, k);
+        second = k % 2 == 0 && !second;
+        n -= k;
+    }
     return LBM_OK;
 }
 
@@ -298,6 +318,55 @@ hipError_t copy_rows(lbm_ctx *c, void *dst, const void *src, size_t elem, hipMem
 int env_int(const char *name, int dflt) {
     const char *v = getenv(name);
     return (v && *v) ? atoi(v) : dflt;
+}
+
+// Workgroup shape, tile and steps per launch of the D2Q9 step: the least estimated time per step.
+// A launch costs about 4 us whatever it does (the gap to the next one, the prologue, the first
+// loads' latency). A workgroup then takes the vector instructions of its nodes, step by step with
+// their halo (0.133 us per 64 nodes and step in FP32, 0.25 in FP64), and its share of the memory
+// traffic (21 GB/s per CU); the two overlap in part. So small grids take several steps of tiny
+// tiles per launch, larger ones two steps of larger tiles. FP64 grids past 200,000 nodes are
+// bound by memory and by the halo's FP64 arithmetic: there one step per launch with a thread per
+// node is faster. Measured us per step: this choice | one thread per node of 64 x 8 tiles:
+//   FP64  64^2 2.6 | 5.0   256^2 4.0 | 5.3   400x380 5.9 | 7.1   512^2 10.5 | 9.8   2040x1900 126 | 121
+//   FP32  64^2 2.2 | 4.0   256^2 3.0 | 4.2   512^2 5.1 | 5.7     1000x900 16.8 | 19     2048^2 63 | 68
+// LBM2P_TILE="threads,nodes per thread,width,height,steps" overrides ("512,0,64,8,1": one thread per node).
+void plan_tiles(lbm_ctx *c, int cus) {
+    static constexpr int shapes[][2] = {{256, 1}, {512, 2}, {512, 3}, {1024, 2}};
+    const int size = c->fp64 ? 8 : 4;
+    D2Shape best{512, 0, 64, 8, 1};
+    double least = -1.0;
+    if (!(c->fp64 && (double)c->g.nx * c->g.ny > 200e3))
+        for (const auto &wg : shapes)
+            for (int tx = 8; tx <= 64; tx += 8)
+                for (int ty = 4; ty <= 32; ty += 4)
+                    for (int steps = 1; steps <= 3; ++steps) {
+                        const D2Shape sh{wg[0], wg[1], tx, ty, steps};
+                        if (!d2_fits(c->fp64, sh) || !d2_launcher(c->fp64, c->masked, sh)) continue;
+                        double waves = 0.0, first = 0.0;
+                        for (int r = 0; r < steps; ++r) {
+                            first = (double)(tx + 4 + 6 * r) * (ty + 4 + 6 * r);
+                            waves += ceil(first / 64.0);
+                        }
+                        const double rounds = ceil(ceil((double)c->g.nx / tx) * ceil((double)c->g.ny / ty) / cus);
+                        if (rounds > 3 && wg[0] == 1024) continue;   // one workgroup per CU: nothing overlaps its barriers
+                        const double compute = (c->fp64 ? 0.25 : 0.133) * waves;
+                        // rows of whole cache lines, unless every CU has a tile of its own (2048^2
+                        // FP32: 24 x 32 tiles 71 us a step, 32 x 24 ones 68)
+                        const double lines = rounds > 1 && tx * size % 128 ? 1.5 : 1.0;
+                        const double memory = lines * (first + tx * ty) * 9.0 * size / 21e3;
+                        const double overlap = c->fp64 && wg[1] == 3 ? 0.79 : 0.72;   // 139 KB of LDS
+                        const double us = (4.0 + overlap * rounds * (compute + memory)) / steps;
+                        if (least < 0.0 || us < least) { least = us; best = sh; }
+                    }
+    const char *e = getenv("LBM2P_TILE");
+    D2Shape w{};
+    if (e && sscanf(e, "%d,%d,%d,%d,%d", &w.threads, &w.per, &w.tx, &w.ty, &w.steps) == 5 && d2_fits(c->fp64, w) &&
+        d2_launcher(c->fp64, c->masked, w))
+        best = w;
+    c->tile_steps = best.steps;
+    for (int k = 1; k <= best.steps; ++k) c->tiles[k - 1] = d2_tiles(c->g, c->fp64, best, k);
+    c->d2 = d2_launcher(c->fp64, c->masked, best);
 }
 
 }  // namespace
@@ -427,8 +496,9 @@ int lbm_create(const lbm_params *p, lbm_ctx **out) {
             if (!c->segs.empty()) c->fused = c->segs[0].fn;
         }
     }
-    // D2Q9 steps in one pass (LBM2P_TWO_PASS=1: the moment pass, then the collide)
-    c->single = c->D == 2 && !env_int("LBM2P_TWO_PASS", 0) && c->ks.single;
+    // D2Q9 steps in tiles (LBM2P_TWO_PASS=1: the moment pass, then the collide)
+    if (c->D == 2 && !env_int("LBM2P_TWO_PASS", 0)) plan_tiles(c, cus);
+    c->graph_steps = std::max(2, kGraphSteps / c->tile_steps / 2 * 2) * c->tile_steps;
     // unfused steps replay captured blocks of steps (LBM2P_GRAPH=0: every step launched)
     c->use_graph = !c->fused && env_int("LBM2P_GRAPH", 1) != 0;
     const size_t N = (size_t)c->g.N;
@@ -447,7 +517,7 @@ int lbm_create(const lbm_params *p, lbm_ctx **out) {
     const size_t pop = (size_t)c->Q * (size_t)c->g.qs * c->sbytes;
     if (hipMalloc(&c->A, pop) != hipSuccess || hipMalloc(&c->B, pop) != hipSuccess ||
         hipMalloc(&c->rho, N * cbytes) != hipSuccess ||
-        (!c->fused && !c->single && hipMalloc(&c->gfl, (size_t)c->D * N * cbytes) != hipSuccess) ||   // two-pass step only
+        (!c->fused && !c->d2 && hipMalloc(&c->gfl, (size_t)c->D * N * cbytes) != hipSuccess) ||   // two-pass step only
         hipMalloc((void **)&c->partials, (size_t)c->nblk * kPartialSlots * sizeof(double)) != hipSuccess ||
         hipMalloc((void **)&c->rscratch, (size_t)std::max(reduce_scratch_rows(c->nblk), reduce_scratch_rows(c->nfslots)) *
                                              kPartialSlots * sizeof(double)) != hipSuccess ||
@@ -591,14 +661,14 @@ int lbm_step_timed(lbm_ctx *c, int64_t n, double ms[3], int64_t launches[2]) {
     HIP_OR_FAIL(c, hipEventRecord(tot0, c->stream));
     for (int64_t t = 0; t < n; ++t) {
         HIP_OR_FAIL(c, hipEventRecord(ev[0], c->stream));
-        if (!c->fused && !c->single)
+        if (!c->fused && !c->d2)
             c->ks.moments(c->stream, c->A, c->g, c->links, params_ptr(c), c->rho, c->gfl, nullptr, nullptr, c->partials);
         HIP_OR_FAIL(c, hipEventRecord(ev[1], c->stream));
         if (c->fused) {
             fused_step(c);
             c->folded = c->fold;
-        } else if (c->single) {
-            c->ks.single(c->stream, c->A, c->B, c->g, c->links, params_ptr(c));
+        } else if (c->d2) {
+            unfused_steps(c, c->stream, c->A, c->B, 1);
         } else {
             c->ks.collide(c->stream, c->A, c->B, c->g, c->links, params_ptr(c), c->rho, c->gfl);
         }
@@ -622,7 +692,7 @@ int lbm_step_timed(lbm_ctx *c, int64_t n, double ms[3], int64_t launches[2]) {
     ms[0] = acc[0];
     ms[1] = acc[1];
     ms[2] = tt;
-    launches[0] = c->fused || c->single ? 0 : n;
+    launches[0] = c->fused || c->d2 ? 0 : n;
     launches[1] = n;
     return LBM_OK;
 }

@@ -1,6 +1,5 @@
-// step_kernels.hip -- the D2Q9 stream-collide step in one pass, and the two-pass step
-// (D3Q27 grids the fused z-march does not take), of the two-phase LBGK model (Sec. 2.3)
-// for gfx950.
+// step_kernels.hip -- the two-pass step (D3Q27 grids the fused z-march does not take) of the
+// two-phase LBGK model (Sec. 2.3), the initial state, output fields and pressure tensor, for gfx950.
 //
 // Storage: structure of arrays A[i*qs + n], n = x + nx*(y + ny*z). The array holds
 // post-collision populations at the node that produced them; every pass pulls
@@ -11,11 +10,10 @@
 // Pass 1 (moments): rho = rho_ref + sum h_i, j = sum c_i h_i, g_a = rho u_a^3; FP64
 //   per-workgroup partial sums of mass and momentum for the watchdog.
 // Pass 2 (collide): stages rho and the signed pseudo-potential of a 64x4xZB tile
-//   plus a two-node halo in LDS (the D2Q9 single pass: a 64x8 tile whose staged nodes
-//   take rho and g from their own pulls), evaluates the two-ring Korteweg force
-//   (eq Kforce_final, or the stencil coefficients of another force model), the diagonal correction Phi (eq correction), the product-form
-//   equilibrium and extended equilibrium (eqs LBMeq, LBMstar) in cancellation-free
-//   deviation form, and the LBGK update (eq LBGK).
+//   plus a two-node halo in LDS, evaluates the two-ring Korteweg force (eq Kforce_final, or
+//   the stencil coefficients of another force model), the diagonal correction Phi (eq
+//   correction), the product-form equilibrium and extended equilibrium (eqs LBMeq, LBMstar)
+//   in cancellation-free deviation form, and the LBGK update (eq LBGK).
 #include <hip/hip_runtime.h>
 #include <math.h>
 
@@ -32,9 +30,6 @@ namespace {
 constexpr int TX = 64;   // tile width in x: one wave64 row, coalesced 256 B (FP32) loads
 constexpr int TY = 4;    // tile height in y: 4 waves per workgroup
 constexpr int HALO = 2;  // two neighbour rings
-constexpr int kSingleTY = 8;   // D2Q9 single pass: tile height (one wave per row)
-constexpr int kXcds = 8;       // MI355X: workgroups are dealt to 8 XCDs in turn
-constexpr int kXcdChunk = 128; // single pass: consecutive tiles per XCD chunk
 
 // ------------------------------------------------------------------ reductions
 __device__ __forceinline__ double wave_sum(double v) {
@@ -127,16 +122,14 @@ __global__ __launch_bounds__(256) void k_links(const uint8_t *__restrict__ mask,
 }
 
 // ------------------------------------------------------------------ pass 2
-// TYT: tile height in y, one wave per row (the D2Q9 single pass takes 8 rows and 512 threads,
-// which stages a halo of 59% of the tile instead of 113%)
-template <int D, int TYT = TY> struct Tile {
+template <int D> struct Tile {
     static constexpr int ZB = D == 3 ? 2 : 1;                  // z-planes per workgroup
-    static constexpr int LX = TX + 2 * HALO, LY = TYT + 2 * HALO;
+    static constexpr int LX = TX + 2 * HALO, LY = TY + 2 * HALO;
     static constexpr int LZ = D == 3 ? ZB + 2 * HALO : 1;
     static constexpr int LS = LX * LY * LZ;
 };
 
-enum { MODE_STEP = 0, MODE_VEL = 1, MODE_INIT = 2, MODE_PT = 3, MODE_SINGLE = 4 };
+enum { MODE_STEP = 0, MODE_VEL = 1, MODE_INIT = 2, MODE_PT = 3 };
 
 // MODE_STEP: one collide-stream step A -> B.
 // MODE_VEL:  U = u + S/(2 rho) in FP64 (user layout), in place of the bare u in out_U (D2Q9).
@@ -147,104 +140,24 @@ enum { MODE_STEP = 0, MODE_VEL = 1, MODE_INIT = 2, MODE_PT = 3, MODE_SINGLE = 4 
 //            momentum flux of the pulled (pre-collision) populations minus the one- and
 //            two-ring pseudo-potential and capillary tensors, which enter with the sign of
 //            the momentum source S = -F.
-// MODE_SINGLE: one collide-stream step A -> B in a single pass (D2Q9): the staged tile and
-//            halo nodes pull their own populations and take rho and g = rho u^3 from them, as
-//            the moment pass computes them, instead of reading the moment pass's fields.
 template <int D, class S, class C, bool MASK, int MODE>
-__global__ __launch_bounds__(MODE == MODE_SINGLE ? TX * kSingleTY : TX * TY) void k_collide(
+__global__ __launch_bounds__(TX *TY) void k_collide(
     const S *__restrict__ A, S *__restrict__ B, Geom g, const uint8_t *__restrict__ mask,
     const uint32_t *__restrict__ links, Params<C> p, const C *__restrict__ rho_f, const C *__restrict__ gf,
     double *__restrict__ out_U) {
     // MODE_INIT has the mask, the others the solid-neighbour bits
-    constexpr bool SINGLE = MODE == MODE_SINGLE;
-    static_assert(!SINGLE || D == 2, "single-pass mode: D2Q9");
-    constexpr int TYK = SINGLE ? kSingleTY : TY, NTH = TX * TYK;
-    using T = Tile<D, TYK>;
+    constexpr int NTH = TX * TY;
+    using T = Tile<D>;
     __shared__ C s_rho[T::LS];
     __shared__ C s_psi[T::LS];
-    __shared__ C s_g[SINGLE ? 2 : 1][SINGLE ? T::LS : 1];   // single pass: g_x, g_y of the staged nodes
-    // single pass: a 1-D grid. The hardware deals workgroups to the 8 XCDs in turn; the tiles,
-    // in row-major order, go to them in chunks of up to kXcdChunk consecutive tiles, so that
-    // neighbouring tiles mostly share an XCD and read each other's halo rows from its L2
-    int bx = blockIdx.x, by = blockIdx.y;
-    if constexpr (SINGLE) {
-        const int ntx = (g.nx + TX - 1) / TX, nt = ntx * ((g.ny + TYK - 1) / TYK);
-        const int per = (nt + kXcds - 1) / kXcds, ch = per < kXcdChunk ? per : kXcdChunk, b = blockIdx.x;
-        const int i = b / kXcds;
-        const int tile = ((i / ch) * kXcds + b % kXcds) * ch + i % ch;
-        if (tile >= nt) return;   // the padding of the last XCD's share (whole workgroup)
-        bx = tile % ntx;
-        by = tile / ntx;
-    }
-    const int x0 = bx * TX, y0 = by * TYK, z0 = D == 3 ? blockIdx.z * T::ZB : 0;
-    // single pass: the populations this thread pulled for its own node, kept for its update
-    C h_own[Lat<D>::Q];
-    if constexpr (SINGLE) {
-        // Staging: every thread its own tile node (wrapped past the grid's edge: those feed the
-        // stencils of the last columns and rows), and at most one of the NH halo nodes: rows 0,
-        // 1, LY-2, LY-1 of the staged tile, then columns 0, 1, LX-2, LX-1 of the rows between.
-        // Both nodes' pulls are issued before either is reduced, with the moment pass's
-        // arithmetic, to rho, s psi and g.
-        const int t = threadIdx.x, tx = t & (TX - 1), ty = t / TX;
-        constexpr int NH = T::LS - NTH;
-        static_assert(NH <= NTH, "one halo node per thread at most");
-        const bool has_halo = t < NH;
-        int lx = 0, ly = 0;
-        if (t < 4 * T::LX) {
-            const int r = t / T::LX;
-            lx = t % T::LX;
-            ly = r < 2 ? r : TYK + r;
-        } else if (has_halo) {
-            const int q = t - 4 * T::LX, c4 = q % 4;
-            ly = 2 + q / 4;
-            lx = c4 < 2 ? c4 : TX + c4;
-        }
-        const int e_own = (ty + HALO) * T::LX + tx + HALO, e_halo = ly * T::LX + lx;
-        const int ox = wrapi(x0 + tx, g.nx), oy = wrapi(y0 + ty, g.ny);
-        const int hx = wrapi(x0 - HALO + lx, g.nx), hy = wrapi(y0 - HALO + ly, g.ny);
-        const int on = ox + g.px * oy, hn = hx + g.px * hy;
-        const uint32_t olm = MASK ? links[on] : 0u, hlm = MASK && has_halo ? links[hn] : 0u;
-        const bool osolid = link_solid(olm), hsolid = link_solid(hlm);
-        C hh[Lat<D>::Q];
-        if (!osolid) {
-            Nbr<D> nb(g, ox, oy, 0);
-            gather_links<D, S, C, MASK>(A, g.qs, olm, nb, on, h_own, p.link_q);
-        }
-        if (has_halo && !hsolid) {
-            Nbr<D> nb(g, hx, hy, 0);
-            gather_links<D, S, C, MASK>(A, g.qs, hlm, nb, hn, hh, p.link_q);
-        }
-        auto finish = [&](int e, int gn, bool solid, const C (&h)[Lat<D>::Q]) __attribute__((always_inline)) {
-            C r, ga[2] = {C(0), C(0)};
-            if (solid) {
-                r = wall_density(p, gn);
-            } else {
-                C sum, j[3];
-                moments_of<D, C>(h, sum, j);
-                r = p.rho_ref + sum;
-                const C rinv = rcp(r);
-#pragma unroll
-                for (int a = 0; a < 2; ++a) {
-                    const C ua = j[a] * rinv;
-                    ga[a] = r * ua * ua * ua;
-                }
-            }
-            s_rho[e] = r;
-            s_psi[e] = signed_psi(p.eos, r);
-            s_g[0][e] = ga[0];
-            s_g[1][e] = ga[1];
-        };
-        finish(e_own, on, osolid, h_own);
-        if (has_halo) finish(e_halo, hn, hsolid, hh);
-    } else {
-        for (int e = threadIdx.x; e < T::LS; e += NTH) {
-            const int lx = e % T::LX, t = e / T::LX, ly = t % T::LY, lz = t / T::LY;
-            const int gx = wrapi(x0 - HALO + lx, g.nx), gy = wrapi(y0 - HALO + ly, g.ny);
-            const int gz = D == 3 ? wrapi(z0 - HALO + lz, g.nz) : 0;
-            const C r = rho_f[gx + g.px * (gy + g.ny * gz)];
-            s_rho[e] = r;
-            s_psi[e] = signed_psi(p.eos, r);
-        }
+    const int x0 = blockIdx.x * TX, y0 = blockIdx.y * TY, z0 = D == 3 ? blockIdx.z * T::ZB : 0;
+    for (int e = threadIdx.x; e < T::LS; e += NTH) {
+        const int lx = e % T::LX, t = e / T::LX, ly = t % T::LY, lz = t / T::LY;
+        const int gx = wrapi(x0 - HALO + lx, g.nx), gy = wrapi(y0 - HALO + ly, g.ny);
+        const int gz = D == 3 ? wrapi(z0 - HALO + lz, g.nz) : 0;
+        const C r = rho_f[gx + g.px * (gy + g.ny * gz)];
+        s_rho[e] = r;
+        s_psi[e] = signed_psi(p.eos, r);
     }
     __syncthreads();
     const int tx = threadIdx.x & (TX - 1), ty = threadIdx.x / TX;
@@ -309,26 +222,39 @@ __global__ __launch_bounds__(MODE == MODE_SINGLE ? TX * kSingleTY : TX * TY) voi
         }
         const int lc = ((D == 3 ? zz + HALO : 0) * T::LY + ty + HALO) * T::LX + tx + HALO;
         const C rho = s_rho[lc], spc = s_psi[lc];
-        C Fp[3] = {C(0), C(0), C(0)}, Fc[3] = {C(0), C(0), C(0)};
-        static_for<1, Lat<D>::Q>([&](auto I) {
-            constexpr int i = decltype(I)::value;
-            constexpr int cx = Lat<D>::c(i, 0), cy = Lat<D>::c(i, 1), cz = Lat<D>::c(i, 2);
-            constexpr int off = (cz * T::LY + cy) * T::LX + cx;
-            constexpr int cls = cx * cx + cy * cy + cz * cz - 1;   // weight class of c_i
-            const C p1 = fabs(s_psi[lc + off]), p2 = fabs(s_psi[lc + 2 * off]);
-            const C r1 = s_rho[lc + off], r2 = s_rho[lc + 2 * off];
-            const C tp = p.gw[cls][0] * p1 + p.gw[cls][1] * p2;   // 3w (G1 psi1 + G2 psi2)
-            const C tc = p.gw[cls][2] * r1 + p.gw[cls][3] * r2;   // 3w (G3 rho1 + G4 rho2)
-            static_for<0, D>([&](auto A_) {
-                constexpr int a = decltype(A_)::value;
-                constexpr int ca = Lat<D>::c(i, a);
-                if constexpr (ca == 1) { Fp[a] += tp; Fc[a] += tc; }
-                if constexpr (ca == -1) { Fp[a] -= tp; Fc[a] -= tc; }
+        C Sf[3] = {C(0), C(0), C(0)};   // S = -F + rho g
+        if constexpr (D == 2) {         // as the D2Q9 tiles
+            const C gw[8] = {p.gw[0][0], p.gw[1][0], p.gw[0][2], p.gw[1][2], p.gw[0][1], p.gw[1][1], p.gw[0][3], p.gw[1][3]};
+            const C accel[2] = {p.accel[0], p.accel[1]};
+            C S2[2];
+            struct Node { C rho, psi; };
+            source_plane<C>(gw, rho, spc, accel, [&](int k, int cx, int cy) __attribute__((always_inline)) {
+                const int e = lc + k * (cx + cy * T::LX);
+                return Node{s_rho[e], s_psi[e]};
+            }, S2);
+            Sf[0] = S2[0];
+            Sf[1] = S2[1];
+        } else {
+            C Fp[3] = {C(0), C(0), C(0)}, Fc[3] = {C(0), C(0), C(0)};
+            static_for<1, Lat<D>::Q>([&](auto I) {
+                constexpr int i = decltype(I)::value;
+                constexpr int cx = Lat<D>::c(i, 0), cy = Lat<D>::c(i, 1), cz = Lat<D>::c(i, 2);
+                constexpr int off = (cz * T::LY + cy) * T::LX + cx;
+                constexpr int cls = cx * cx + cy * cy + cz * cz - 1;   // weight class of c_i
+                const C p1 = fabs(s_psi[lc + off]), p2 = fabs(s_psi[lc + 2 * off]);
+                const C r1 = s_rho[lc + off], r2 = s_rho[lc + 2 * off];
+                const C tp = p.gw[cls][0] * p1 + p.gw[cls][1] * p2;   // 3w (G1 psi1 + G2 psi2)
+                const C tc = p.gw[cls][2] * r1 + p.gw[cls][3] * r2;   // 3w (G3 rho1 + G4 rho2)
+                static_for<0, D>([&](auto A_) {
+                    constexpr int a = decltype(A_)::value;
+                    constexpr int ca = Lat<D>::c(i, a);
+                    if constexpr (ca == 1) { Fp[a] += tp; Fc[a] += tc; }
+                    if constexpr (ca == -1) { Fp[a] -= tp; Fc[a] -= tc; }
+                });
             });
-        });
-        C Sf[3] = {C(0), C(0), C(0)};
 #pragma unroll
-        for (int a = 0; a < D; ++a) Sf[a] = rho * p.accel[a] - (C(2) * spc * Fp[a] + rho * Fc[a]);   // S = -F + rho g
+            for (int a = 0; a < D; ++a) Sf[a] = rho * p.accel[a] - (C(2) * spc * Fp[a] + rho * Fc[a]);
+        }
 
         if constexpr (MODE == MODE_VEL) {
             const int un = x + g.nx * (y + g.ny * z);
@@ -368,12 +294,7 @@ __global__ __launch_bounds__(MODE == MODE_SINGLE ? TX * kSingleTY : TX * TY) voi
             });
             continue;
         } else {
-        if constexpr (SINGLE) {
-#pragma unroll
-            for (int i = 0; i < Lat<D>::Q; ++i) h[i] = h_own[i];
-        } else {
-            gather_links<D, S, C, MASK>(A, g.qs, lm, nb, n, h, p.link_q);
-        }
+        gather_links<D, S, C, MASK>(A, g.qs, lm, nb, n, h, p.link_q);
         C drho, j[3];
         moments_of<D, C>(h, drho, j);
         C u[3] = {C(0), C(0), C(0)};
@@ -382,18 +303,17 @@ __global__ __launch_bounds__(MODE == MODE_SINGLE ? TX * kSingleTY : TX * TY) voi
         for (int a = 0; a < D; ++a) u[a] = j[a] * rinv;
         const C omega = omega_of(p, rho);
         C Phi[3] = {C(0), C(0), C(0)};
-        if constexpr (SINGLE) {
-            const C cf = (C(1) - C(0.5) * omega) * C(0.5);
-            Phi[0] = cf * (s_g[0][lc + 1] - s_g[0][lc - 1]);
-            Phi[1] = cf * (s_g[1][lc + T::LX] - s_g[1][lc - T::LX]);
+        const C cf = (C(1) - C(0.5) * omega) * C(0.5);
+        Phi[0] = cf * (gf[nb.at(1, 0, 0)] - gf[nb.at(-1, 0, 0)]);
+        Phi[1] = cf * (gf[(long long)g.N + nb.at(0, 1, 0)] - gf[(long long)g.N + nb.at(0, -1, 0)]);
+        if constexpr (D == 3)
+            Phi[2] = cf * (gf[2LL * g.N + nb.at(0, 0, 1)] - gf[2LL * g.N + nb.at(0, 0, -1)]);
+        if constexpr (D == 2) {
+            const C j2[2] = {j[0], j[1]}, S2[2] = {Sf[0], Sf[1]}, P2[2] = {Phi[0], Phi[1]};
+            update_plane<C>(h, rho, drho, rinv, j2, S2, P2, omega);
         } else {
-            const C cf = (C(1) - C(0.5) * omega) * C(0.5);
-            Phi[0] = cf * (gf[nb.at(1, 0, 0)] - gf[nb.at(-1, 0, 0)]);
-            Phi[1] = cf * (gf[(long long)g.N + nb.at(0, 1, 0)] - gf[(long long)g.N + nb.at(0, -1, 0)]);
-            if constexpr (D == 3)
-                Phi[2] = cf * (gf[2LL * g.N + nb.at(0, 0, 1)] - gf[2LL * g.N + nb.at(0, 0, -1)]);
+            collide<D, C>(h, rho, drho, u, Sf, Phi, omega);
         }
-        collide<D, C>(h, rho, drho, u, Sf, Phi, omega);
         static_for<0, Lat<D>::Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
             st_nt_at(B + i * g.qs, (unsigned)n, S(h[i]));
@@ -596,13 +516,6 @@ dim3 moment_grid(int D, const Geom &g) {
     return dim3((g.nx + TX - 1) / TX, (g.ny + TY - 1) / TY, D == 3 ? g.nz : 1);
 }
 
-// workgroups of the single pass: its tiles, padded to a whole number per XCD
-inline unsigned single_blocks(const Geom &g) {
-    const long long nt = (long long)((g.nx + TX - 1) / TX) * ((g.ny + kSingleTY - 1) / kSingleTY);
-    const long long per = (nt + kXcds - 1) / kXcds, ch = per < kXcdChunk ? per : kXcdChunk;
-    return (unsigned)((per + ch - 1) / ch * ch * kXcds);
-}
-
 template <int D, class S, class C, bool MASK> struct Launch {
     static dim3 collide_grid(const Geom &g) {
         return dim3((g.nx + TX - 1) / TX, (g.ny + TY - 1) / TY, D == 3 ? (g.nz + Tile<D>::ZB - 1) / Tile<D>::ZB : 1);
@@ -638,12 +551,6 @@ template <int D, class S, class C, bool MASK> struct Launch {
         hipLaunchKernelGGL((k_collide<D, S, C, MASK, MODE_STEP>), collide_grid(g), dim3(256), 0, s, (const S *)A, (S *)B, g,
                            nullptr, links, *(const Params<C> *)prm, (const C *)rho, (const C *)gfl, nullptr);
     }
-    static void single(hipStream_t s, const void *A, void *B, const Geom &g, const uint32_t *links, const void *prm) {
-        if constexpr (D == 2)
-            hipLaunchKernelGGL((k_collide<D, S, C, MASK, MODE_SINGLE>), dim3(single_blocks(g)),
-                               dim3(TX * kSingleTY), 0, s, (const S *)A, (S *)B, g, nullptr, links,
-                               *(const Params<C> *)prm, (const C *)nullptr, (const C *)nullptr, nullptr);
-    }
     static void pressure(hipStream_t s, const void *A, const Geom &g, const uint32_t *links, const void *prm,
                          const void *rho, double *out) {
         hipLaunchKernelGGL((k_collide<D, S, C, MASK, MODE_PT>), collide_grid(g), dim3(256), 0, s, (const S *)A,
@@ -672,7 +579,6 @@ template <int D, class S, class C, bool MASK> struct Launch {
         k.init = init;
         k.moments = moments;
         k.collide = collide;
-        k.single = D == 2 ? single : nullptr;
         k.links = make_links;
         k.velocity = velocity;
         k.pressure = pressure;

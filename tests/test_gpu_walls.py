@@ -44,6 +44,43 @@ def _random_walls(D, nx, ny, nz, seed, lo=0.05, hi=0.95):
     return case, rho0, u0, (rv, rl)
 
 
+_TILES = ["256,1,8,4,2", "512,2,16,16,3", "512,3,32,24,2", "512,3,24,20,3", "1024,2,32,32,2", "512,0,64,8,1"]
+
+
+@pytest.mark.parametrize("walls", ["none", "halfway", "interpolated"])
+@pytest.mark.parametrize("dims", [(37, 29), (130, 61), (64, 24), (5, 3), (1, 9)])
+def test_d2q9_tiles_of_several_steps(dims, walls, monkeypatch):
+    # Every workgroup shape of the D2Q9 tiles, with tiles that divide the grid, do not, and exceed
+    # it, against the two-pass step: the same arithmetic, so agreement to rounding (bounds of the
+    # test above). How a run is cut into calls, and so into launches of one, two or three steps,
+    # must not change a bit.
+    import paper_2112_01975_amd as P
+    nx, ny = dims
+    case, rho0, u0, (rv, rl) = _random_walls(2, nx, ny, 1, 75)
+    if walls == "none":
+        case = Case(2, nx, ny, a=0.02, T_reduced=0.8)
+    elif walls == "halfway":
+        wall = np.linspace(0.3 * rl, 0.6 * rl, nx * ny)
+        case = Case(2, nx, ny, a=0.02, T_reduced=0.8, rho_wall=case.rho_wall, mask=case.mask, rho_wall_field=wall)
+    for prec in (0, 1):
+        monkeypatch.setenv("LBM2P_TWO_PASS", "1")
+        ref = P.Simulation(case.params(prec, rv if prec else 0.0)).init(rho0, u0).step(20).moments()
+        monkeypatch.setenv("LBM2P_TWO_PASS", "0")
+        tr, tu = (1e-12, 1e-12) if prec == 0 else (1e-5, 1e-6)
+        for tile in _TILES:
+            monkeypatch.setenv("LBM2P_TILE", tile)
+            pops = []
+            for calls in ((20,), (1, 7, 2, 10)):
+                with P.Simulation(case.params(prec, rv if prec else 0.0)) as s:
+                    s.init(rho0, u0)
+                    for n in calls:
+                        s.step(n)
+                    pops.append(P.lbm_get_populations(s.ctx))
+                    r, U, _ = s.moments()
+            assert np.array_equal(pops[0], pops[1]), tile
+            assert max_rel(r, ref[0]) < tr and np.abs(U - ref[1]).max() < tu, (tile, prec)
+
+
 @pytest.mark.parametrize("walls", ["none", "halfway", "interpolated"])
 @pytest.mark.parametrize("prec", [0, 1])
 def test_d2q9_single_pass_matches_two_pass(walls, prec, monkeypatch):
