@@ -408,7 +408,7 @@ int lbm_create(const lbm_params *p, lbm_ctx **out) {
     // LBM2P_FUSED_TX / _TY / _TZ override the tile shape and z-chunk length). By default
     // the z-chunks are as long as possible while every CU still gets a work item: each
     // chunk re-reads a four-plane z halo and runs a five-plane prologue.
-    const int tx = env_int("LBM2P_FUSED_TX", 64), ty = env_int("LBM2P_FUSED_TY", 8);
+    int tx = env_int("LBM2P_FUSED_TX", 64), ty = env_int("LBM2P_FUSED_TY", 8);
     int cus = 256;
     {
         int dev = 0, n = 0;
@@ -416,30 +416,52 @@ int lbm_create(const lbm_params *p, lbm_ctx **out) {
             hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
             cus = n;
     }
-    const long long tiles = (long long)((c->g.nx + tx - 1) / tx) * ((c->g.ny + ty - 1) / ty);
-    // Small grids: a work item marches its planes one after another, so when even 16-plane
-    // z-chunks give fewer items than CUs, the two-pass step, parallel over all nodes, is
-    // faster (per step, FP32 at 32^3, 64^3, 96^3: 94, 90, 104 us single-pass against 17, 25,
-    // 84 two-pass; FP64 162, 178, 211 against 22, 50, 200; at 128^3 the single pass wins, 129
-    // against 162 FP32). LBM2P_FUSED=1 takes the single-pass step at any size.
-    const bool few_items = tiles * std::max(1, c->g.nz / 16) < cus;
+    auto tile_count = [&](int wx, int wy) { return (long long)((c->g.nx + wx - 1) / wx) * ((c->g.ny + wy - 1) / wy); };
+    // Chunk length for a run of len planes in tiles columns. Each work item (tile x chunk) marches
+    // its planes after a five-plane prologue; items run in rounds of one per CU. The number of
+    // chunks minimises rounds x (planes per chunk + 6), the returned cost, with chunks of >= least
+    // planes: long chunks, but no last round that leaves most CUs idle (288 tiles on 256 CUs in
+    // one chunk would take two full rounds' time for 1.1 rounds' work). Chunks stay within
+    // 320 planes: over longer marches neighbouring tiles drift apart in z and the halo
+    // lines they share leave L2 between the two reads (600^3: 600-plane chunks 14.7,
+    // 300-plane chunks 15.2 GLUPS).
+    auto split = [&](long long tiles, int len, int least, long long *nchunks) {
+        long long cost = -1;
+        for (long long nzc = std::max(1, (len + 319) / 320); nzc <= std::max(1, len / least); ++nzc) {
+            const long long rounds = (tiles * nzc + cus - 1) / cus;
+            const long long k = rounds * ((len + nzc - 1) / nzc + 6);
+            if (cost < 0 || k < cost) { cost = k; *nchunks = nzc; }
+        }
+        return cost;
+    };
+    // Small grids: a work item marches its planes one after another, so a grid too small to give
+    // every CU an item of some planes is faster in the two-pass step, parallel over all nodes.
+    // One plane of the single pass takes about 4.9 us in FP32 and 10.1 in FP64, the two passes
+    // 0.094 and 0.22 us per 1000 nodes; near the line, single pass | two passes, us per step:
+    // 64^3 FP32 90 | 25, FP64 178 | 52; 96^3 FP32 77 | 84, FP64 161 | 200 (10-plane chunks). With
+    // walls, whose planes cost more, the line is 16-plane chunks for every CU. LBM2P_FUSED=1
+    // takes the single-pass step at any size.
+    const bool plain_box = c->D == 3 && !c->masked;
+    const int nzg = c->g.nz;
+    long long nz64 = 1, nz32 = 1;
+    const long long tiles64 = tile_count(64, 8), cost64 = split(tiles64, nzg, 4, &nz64);
+    const double single_us = (c->fp64 ? 10.1 : 4.9) * (double)cost64, two_us = (c->fp64 ? 0.22e-3 : 0.094e-3) * (double)c->g.N;
+    const bool few_items = plain_box ? single_us > two_us : tiles64 * std::max(1, nzg / 16) < cus;
+    // FP32 boxes without walls also have 32 x 16 tiles: 15% slower per plane (more misaligned
+    // lines, less halo), but some widths waste fewer lanes and items with them
+    // (150x141x130 228 -> 216 us a step, 224x100x180 304 -> 288)
+    if (plain_box && !c->fp64 && !getenv("LBM2P_FUSED_TX") && !getenv("LBM2P_FUSED_TY") &&
+        !env_int("LBM2P_FUSED_GROUPED", 0) && 27ull * (unsigned long long)c->g.qs * c->sbytes < 0xFFFFFFFFull &&
+        1.15 * (double)split(tile_count(32, 16), nzg, 4, &nz32) < (double)cost64) {
+        tx = 32;
+        ty = 16;
+    }
+    const long long tiles = tile_count(tx, ty);
     if (c->D == 3 && !env_int("LBM2P_TWO_PASS", 0) && (!few_items || env_int("LBM2P_FUSED", 0))) {
-        // Chunk length for a run of len planes. Each work item (tile x chunk) marches its
-        // planes after a five-plane prologue; items run in rounds of one per CU. The number
-        // of chunks minimises rounds x (planes per chunk + 6), chunks of >= least planes: long
-        // chunks, but no last round that leaves most CUs idle (288 tiles on 256 CUs in one
-        // chunk would take two full rounds' time for 1.1 rounds' work). Chunks stay within
-        // 320 planes: over longer marches neighbouring tiles drift apart in z and the halo
-        // lines they share leave L2 between the two reads (600^3: 600-plane chunks 14.7,
-        // 300-plane chunks 15.2 GLUPS).
         auto chunk = [&](int len, int least) {
-            long long best = 1, cost = -1;
-            for (long long nzc = std::max(1, (len + 319) / 320); nzc <= std::max(1, len / least); ++nzc) {
-                const long long rounds = (tiles * nzc + cus - 1) / cus;
-                const long long c = rounds * ((len + nzc - 1) / nzc + 6);
-                if (cost < 0 || c < cost) { cost = c; best = nzc; }
-            }
-            const int tz = env_int("LBM2P_FUSED_TZ", (int)((len + best - 1) / best));
+            long long nchunks = 1;
+            (void)split(tiles, len, least, &nchunks);
+            const int tz = env_int("LBM2P_FUSED_TZ", (int)((len + nchunks - 1) / nchunks));
             return tz > 0 ? tz : 32;
         };
         // the fused kernel addresses a lattice through one buffer resource, through two
@@ -456,7 +478,7 @@ int lbm_create(const lbm_params *p, lbm_ctx **out) {
                                                 : nullptr;
             const int nz = c->g.nz;
             if (!c->masked) {
-                if (plain) c->segs.push_back({plain, fused_grid(c->g, tx, ty, chunk(nz, 16), 0, nz)});
+                if (plain) c->segs.push_back({plain, fused_grid(c->g, tx, ty, chunk(nz, 4), 0, nz)});
             } else if (walls) {
                 // A plane is collided, staged and pulled from within three planes of itself,
                 // so planes with no solid node in z-3..z+3 run the unmasked kernel; maximal

@@ -540,6 +540,28 @@ def test_output_fields_at_tile_and_chunk_edges_match_the_oracle(dims, masked):
         assert max_rel(r_g, r_o) < 1e-10 and np.abs(U_g - U_o).max() < 1e-10
 
 
+@pytest.mark.parametrize("dims", [(150, 20, 24), (33, 17, 9), (96, 96, 32), (32, 16, 4)])
+def test_fused_tiles_of_32x16_agree_bit_for_bit(dims, monkeypatch):
+    # the tile shape changes which thread computes a node, not its arithmetic: FP32 populations of
+    # 32 x 16 and 64 x 8 tiles are the same bits, on grids the tiles divide and do not, with the
+    # z-chunks of a few planes that small boxes take and with one chunk
+    import paper_2112_01975_amd as P
+    nx, ny, nz = dims
+    case = Case(3, nx, ny, nz, eos=T.PR, a=0.005046, acentric=0.344, T_reduced=0.6)
+    rv, rl = case.coexistence()
+    rho0 = L.drop(nx, ny, nz, min(dims) / 4, rl, rv, 5.0, noise=1e-5, seed=1013)
+    pops = []
+    for tx, ty, tz in ((64, 8, 320), (64, 8, 4), (32, 16, 4), (32, 16, 320)):
+        monkeypatch.setenv("LBM2P_FUSED_TX", str(tx))
+        monkeypatch.setenv("LBM2P_FUSED_TY", str(ty))
+        monkeypatch.setenv("LBM2P_FUSED_TZ", str(tz))
+        with P.Simulation(case.params(1, rv)) as s:
+            s.init(rho0).step(12)
+            pops.append(P.lbm_get_populations(s.ctx))
+    for p in pops[1:]:
+        assert np.array_equal(pops[0], p)
+
+
 # ---------------------------------------------------------------- batched sweep
 def _sweep_cases(n, steps_len_lo=32, steps_len_hi=96):
     """A reduced temperature sweep: D2Q9 4 x L flat interfaces, FP64 from T/Tc >= 0.95."""
