@@ -11,7 +11,7 @@ namespace lbm {
 
 struct FusedGrid {
     int tx, ty, tz;        // tile width in x, height in y, planes per z-chunk
-    int zb, ze;            // the launch collides planes [zb, ze) mod nz, in chunks of tz from zb
+    int zb, ze;            // the launch collides planes [zb, ze) (masked: mod nz), in chunks of tz from zb
     int ntx, nty, nzc;     // tiles in x, y and z-chunks
     int items;             // ntx * nty * nzc work items
     int item0, count;      // this launch runs items [item0, item0 + count)

@@ -497,8 +497,15 @@ int lbm_create(const lbm_params *p, lbm_ctx **out) {
                 for (int zb = z0; zb < z0 + nz;) {
                     int ze = zb + 1;
                     while (ze < z0 + nz && near[ze % nz] == near[zb % nz]) ++ze;
-                    const FusedLaunch fn = near[zb % nz] || !plain ? walls : plain;
-                    c->segs.push_back({fn, fused_grid(c->g, tx, ty, chunk(ze - zb, 2), zb, ze)});
+                    auto run = [&](FusedLaunch fn, int b, int e) {
+                        if (e > b) c->segs.push_back({fn, fused_grid(c->g, tx, ty, chunk(e - b, 2), b, e)});
+                    };
+                    if (near[zb % nz] || !plain) {
+                        run(walls, zb % nz, zb % nz + ze - zb);
+                    } else {   // an unmasked launch stays below nz
+                        run(plain, zb, std::min(ze, nz));
+                        run(plain, std::max(zb, nz) - nz, std::max(ze, nz) - nz);
+                    }
                     zb = ze;
                 }
             }
