@@ -1,0 +1,130 @@
+// host_copy.hip -- pageable copies through pinned buffers and worker threads.
+#include <hip/hip_runtime.h>
+#include <sched.h>
+#include <string.h>
+
+#include <algorithm>
+#include <atomic>
+#include <mutex>
+#include <thread>
+#include <vector>
+
+#include "host_copy.hpp"
+
+namespace lbm {
+
+namespace {
+
+constexpr int kWorkers = 8;
+constexpr size_t kChunk = size_t(4) << 20;
+
+std::mutex g_mu;            // holders and the buffers
+int g_holders = 0;
+bool g_busy = false;        // one staged copy at a time; another thread's copy meanwhile goes directly
+void *g_buf[kWorkers] = {};
+
+int worker_count() {
+    cpu_set_t set;
+    const int cpus = sched_getaffinity(0, sizeof set, &set) == 0 ? CPU_COUNT(&set) : 1;
+    return std::max(1, std::min(kWorkers, cpus / 2));
+}
+
+// allocation and waits here leave a capture on another thread's stream alone
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+// takes the buffers (allocating those missing), or returns false
+bool take(int n) {
+    RelaxedCapture relaxed;
+    std::lock_guard<std::mutex> lk(g_mu);
+    if (g_busy || g_holders == 0) return false;
+    for (int w = 0; w < n; ++w)
+        if (!g_buf[w] && hipHostMalloc(&g_buf[w], kChunk, hipHostMallocPortable) != hipSuccess) {
+            g_buf[w] = nullptr;
+            (void)hipGetLastError();
+            return false;
+        }
+    g_busy = true;
+    return true;
+}
+
+void give() {
+    std::lock_guard<std::mutex> lk(g_mu);
+    g_busy = false;
+}
+
+// device, managed and pinned memory is copied directly
+bool pageable(const void *p) {
+    hipPointerAttribute_t a{};
+    const hipError_t e = hipPointerGetAttributes(&a, p);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e == hipErrorInvalidValue || (e == hipSuccess && a.type == hipMemoryTypeUnregistered);
+}
+
+bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
+}
+
+}  // namespace
+
+void staging_hold() {
+    std::lock_guard<std::mutex> lk(g_mu);
+    ++g_holders;
+}
+
+void staging_release() {
+    std::lock_guard<std::mutex> lk(g_mu);
+    if (--g_holders > 0) return;
+    for (void *&b : g_buf) {
+        if (b) (void)hipHostFree(b);
+        b = nullptr;
+    }
+}
+
+hipError_t copy_pageable(int dev, hipStream_t stream, void *dst, const void *src, size_t bytes, hipMemcpyKind kind) {
+    const int n = (int)std::min<size_t>((size_t)worker_count(), (bytes + kChunk - 1) / kChunk);
+    const void *host = kind == hipMemcpyHostToDevice ? src : dst;
+    if (n < 2 || capturing(stream) || !pageable(host) || !take(n)) return hipMemcpyAsync(dst, src, bytes, kind, stream);
+    std::atomic<size_t> next{0};
+    std::atomic<int> err{(int)hipSuccess};
+    auto work = [&](int w) {
+        RelaxedCapture relaxed;
+        hipError_t e = hipSetDevice(dev);
+        hipEvent_t ev = nullptr;
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+        while (e == hipSuccess && err.load() == (int)hipSuccess) {
+            const size_t at = next.fetch_add(kChunk);
+            if (at >= bytes) break;
+            const size_t len = std::min(kChunk, bytes - at);
+            if (kind == hipMemcpyHostToDevice) {
+                memcpy(g_buf[w], (const char *)src + at, len);
+                e = hipMemcpyAsync((char *)dst + at, g_buf[w], len, kind, stream);
+            } else {
+                e = hipMemcpyAsync(g_buf[w], (const char *)src + at, len, kind, stream);
+            }
+            if (e == hipSuccess) e = hipEventRecord(ev, stream);
+            if (e == hipSuccess) e = hipEventSynchronize(ev);
+            else (void)hipStreamSynchronize(stream);   // the buffer may be in use
+            if (e == hipSuccess && kind == hipMemcpyDeviceToHost) memcpy((char *)dst + at, g_buf[w], len);
+        }
+        if (e != hipSuccess) err.store((int)e);
+        if (ev) (void)hipEventDestroy(ev);
+    };
+    std::vector<std::thread> threads;
+    try {
+        threads.reserve((size_t)n - 1);
+        for (int w = 1; w < n; ++w) threads.emplace_back(work, w);
+    } catch (...) {
+        // fewer threads than asked for: the ones there are take all the chunks
+    }
+    work(0);
+    for (std::thread &t : threads) t.join();
+    give();
+    return (hipError_t)err.load();
+}
+
+}  // namespace lbm

@@ -14,6 +14,7 @@
 #include "../../include/lbm2p.h"
 #include "d2q9.hpp"
 #include "fused.hpp"
+#include "host_copy.hpp"
 #include "kernels.hpp"
 #include "runtime_common.hpp"
 #include "thermo_host.hpp"
@@ -124,6 +125,7 @@ void free_ctx(lbm_ctx *c) {
     if (c->htot) (void)hipHostFree(c->htot);
     if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
     if (c->own) (void)hipStreamDestroy(c->own);
+    staging_release();
     delete c;
 }
 
@@ -293,7 +295,7 @@ hipError_t copy_rows(lbm_ctx *c, void *dst, const void *src, size_t elem, hipMem
     const size_t upitch = (size_t)c->g.nx * elem, dpitch = (size_t)c->g.px * elem;
     const size_t rows = (size_t)c->g.ny * c->g.nz, bytes = upitch * rows;
     if (upitch == dpitch)   // unpadded rows: one contiguous copy
-        return hipMemcpyAsync(dst, src, bytes, kind, c->stream);
+        return copy_pageable(c->device, c->stream, dst, src, bytes, kind);
     // padded rows: repack on the device through a contiguous buffer and copy that in one
     // piece (a 2D copy to pageable host memory goes row by row, ~0.3 GB/s)
     hipError_t e;
@@ -304,7 +306,7 @@ hipError_t copy_rows(lbm_ctx *c, void *dst, const void *src, size_t elem, hipMem
     const long long words = (long long)(upitch / 4), up = words, dp = (long long)(dpitch / 4);
     const dim3 grid((unsigned)((words * (long long)rows + 255) / 256));
     if (to_dev) {
-        if ((e = hipMemcpyAsync(c->pack, src, bytes, kind, c->stream)) != hipSuccess) return e;
+        if ((e = copy_pageable(c->device, c->stream, c->pack, src, bytes, kind)) != hipSuccess) return e;
         hipLaunchKernelGGL(k_repitch, grid, dim3(256), 0, c->stream, (const uint32_t *)c->pack, (uint32_t *)dst, words,
                            up, dp, (long long)rows);
         return hipGetLastError();
@@ -312,7 +314,7 @@ hipError_t copy_rows(lbm_ctx *c, void *dst, const void *src, size_t elem, hipMem
     hipLaunchKernelGGL(k_repitch, grid, dim3(256), 0, c->stream, (const uint32_t *)src, (uint32_t *)c->pack, words, dp,
                        up, (long long)rows);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    return hipMemcpyAsync(dst, c->pack, bytes, kind, c->stream);
+    return copy_pageable(c->device, c->stream, dst, c->pack, bytes, kind);
 }
 
 int env_int(const char *name, int dflt) {
@@ -380,6 +382,7 @@ int lbm_create(const lbm_params *p, lbm_ctx **out) {
     if (!validate_params(p, &why)) return fail(nullptr, LBM_E_INVAL, why);
     lbm_ctx *c = new (std::nothrow) lbm_ctx;
     if (!c) return fail(nullptr, LBM_E_NOMEM, "host allocation failed");
+    staging_hold();
     c->p = *p;
     c->p.mask = nullptr;
     c->p.rho_wall_field = nullptr;
@@ -395,7 +398,7 @@ int lbm_create(const lbm_params *p, lbm_ctx **out) {
         const int nx = p->nx, nz = c->D == 3 ? p->nz : 1;
         const int px = (nx >= 64 || env_int("LBM2P_PITCH_ALL", 0)) ? (nx + 31) / 32 * 32 : nx;
         if ((double)px * p->ny * nz >= 2147483647.0) {
-            delete c;
+            free_ctx(c);
             return fail(nullptr, LBM_E_INVAL, "grid larger than 2^31 nodes with its rows padded");
         }
         c->g = make_geom(nx, p->ny, nz, px);
@@ -634,9 +637,9 @@ int lbm_create(const lbm_params *p, lbm_ctx **out) {
 int lbm_init_fields(lbm_ctx *c, const double *rho, const double *u) {
     if (!c || !rho) return fail(c, LBM_E_INVAL, "context or rho is NULL");
     const size_t N = (size_t)c->g.N, Nu = user_nodes(c);
-    for (size_t n = 0; n < Nu; ++n) {
-        if (!(rho[n] > 0.0) || !isfinite(rho[n])) return fail(c, LBM_E_DOMAIN, "initial density must be finite and > 0");
-    }
+    size_t bad = 0;   // no early exit, so that the loop vectorises
+    for (size_t n = 0; n < Nu; ++n) bad += !(rho[n] > 0.0) | !(rho[n] <= 1.7976931348623157e308);
+    if (bad) return fail(c, LBM_E_DOMAIN, "initial density must be finite and > 0");
     HIP_OR_FAIL(c, copy_rows(c, c->io, rho, sizeof(double), hipMemcpyHostToDevice));
     if (u)
         for (int a = 0; a < c->D; ++a)
@@ -736,8 +739,8 @@ int lbm_moments(lbm_ctx *c, double *rho, double *U, double totals[4]) {
     const int rc = reduce_rows(c, c->partials, c->nblk, t);
     if (rc) return rc;
     if (totals) for (int k = 0; k < 4; ++k) totals[k] = t[k];
-    if (rho) HIP_OR_FAIL(c, hipMemcpyAsync(rho, orho, Nu * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-    if (U) HIP_OR_FAIL(c, hipMemcpyAsync(U, oU, (size_t)c->D * Nu * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+    if (rho) HIP_OR_FAIL(c, copy_pageable(c->device, c->stream, rho, orho, Nu * sizeof(double), hipMemcpyDeviceToHost));
+    if (U) HIP_OR_FAIL(c, copy_pageable(c->device, c->stream, U, oU, (size_t)c->D * Nu * sizeof(double), hipMemcpyDeviceToHost));
     if (rho || U) HIP_OR_FAIL(c, hipStreamSynchronize(c->stream));
     return LBM_OK;
 }
@@ -773,7 +776,9 @@ int lbm_pressure_tensor(lbm_ctx *c, double *P) {
     if (rc) return rc;
     c->ks.pressure(c->stream, c->A, c->g, c->links, params_ptr(c), c->rho, c->ptens);
     HIP_OR_FAIL(c, hipGetLastError());
-    for (int k = 0; k < nc; ++k)
+    if (Nu == N)
+        HIP_OR_FAIL(c, copy_pageable(c->device, c->stream, P, c->ptens, (size_t)nc * N * sizeof(double), hipMemcpyDeviceToHost));
+    for (int k = 0; k < nc && Nu != N; ++k)
         HIP_OR_FAIL(c, copy_rows(c, P + (size_t)k * Nu, c->ptens + (size_t)k * N, sizeof(double), hipMemcpyDeviceToHost));
     HIP_OR_FAIL(c, hipStreamSynchronize(c->stream));
     return LBM_OK;
