@@ -16,12 +16,13 @@ namespace lbm {
 namespace {
 
 constexpr int kWorkers = 8;
-constexpr size_t kChunk = size_t(4) << 20;
+constexpr size_t kChunk = size_t(2) << 20;   // pinning memory takes a new context's first copy about 0.2 ms per MiB
+constexpr size_t kLeast = size_t(4) << 20;   // smaller copies are not worth the threads
 
-std::mutex g_mu;            // holders and the buffers
+std::mutex g_mu;            // holders and the buffer
 int g_holders = 0;
 bool g_busy = false;        // one staged copy at a time; another thread's copy meanwhile goes directly
-void *g_buf[kWorkers] = {};
+char *g_buf = nullptr;      // a chunk for each worker
 
 int worker_count() {
     cpu_set_t set;
@@ -36,17 +37,16 @@ struct RelaxedCapture {
     ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
 };
 
-// takes the buffers (allocating those missing), or returns false
-bool take(int n) {
+// takes the buffer (allocating it if missing), or returns false
+bool take() {
     RelaxedCapture relaxed;
     std::lock_guard<std::mutex> lk(g_mu);
     if (g_busy || g_holders == 0) return false;
-    for (int w = 0; w < n; ++w)
-        if (!g_buf[w] && hipHostMalloc(&g_buf[w], kChunk, hipHostMallocPortable) != hipSuccess) {
-            g_buf[w] = nullptr;
-            (void)hipGetLastError();
-            return false;
-        }
+    if (!g_buf && hipHostMalloc((void **)&g_buf, kWorkers * kChunk, hipHostMallocPortable) != hipSuccess) {
+        g_buf = nullptr;
+        (void)hipGetLastError();
+        return false;
+    }
     g_busy = true;
     return true;
 }
@@ -79,20 +79,19 @@ void staging_hold() {
 void staging_release() {
     std::lock_guard<std::mutex> lk(g_mu);
     if (--g_holders > 0) return;
-    for (void *&b : g_buf) {
-        if (b) (void)hipHostFree(b);
-        b = nullptr;
-    }
+    if (g_buf) (void)hipHostFree(g_buf);
+    g_buf = nullptr;
 }
 
 hipError_t copy_pageable(int dev, hipStream_t stream, void *dst, const void *src, size_t bytes, hipMemcpyKind kind) {
     const int n = (int)std::min<size_t>((size_t)worker_count(), (bytes + kChunk - 1) / kChunk);
     const void *host = kind == hipMemcpyHostToDevice ? src : dst;
-    if (n < 2 || capturing(stream) || !pageable(host) || !take(n)) return hipMemcpyAsync(dst, src, bytes, kind, stream);
+    if (bytes <= kLeast || n < 2 || capturing(stream) || !pageable(host) || !take()) return hipMemcpyAsync(dst, src, bytes, kind, stream);
     std::atomic<size_t> next{0};
     std::atomic<int> err{(int)hipSuccess};
     auto work = [&](int w) {
         RelaxedCapture relaxed;
+        char *const buf = g_buf + (size_t)w * kChunk;
         hipError_t e = hipSetDevice(dev);
         hipEvent_t ev = nullptr;
         if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
@@ -101,15 +100,15 @@ hipError_t copy_pageable(int dev, hipStream_t stream, void *dst, const void *src
             if (at >= bytes) break;
             const size_t len = std::min(kChunk, bytes - at);
             if (kind == hipMemcpyHostToDevice) {
-                memcpy(g_buf[w], (const char *)src + at, len);
-                e = hipMemcpyAsync((char *)dst + at, g_buf[w], len, kind, stream);
+                memcpy(buf, (const char *)src + at, len);
+                e = hipMemcpyAsync((char *)dst + at, buf, len, kind, stream);
             } else {
-                e = hipMemcpyAsync(g_buf[w], (const char *)src + at, len, kind, stream);
+                e = hipMemcpyAsync(buf, (const char *)src + at, len, kind, stream);
             }
             if (e == hipSuccess) e = hipEventRecord(ev, stream);
             if (e == hipSuccess) e = hipEventSynchronize(ev);
             else (void)hipStreamSynchronize(stream);   // the buffer may be in use
-            if (e == hipSuccess && kind == hipMemcpyDeviceToHost) memcpy((char *)dst + at, g_buf[w], len);
+            if (e == hipSuccess && kind == hipMemcpyDeviceToHost) memcpy((char *)dst + at, buf, len);
         }
         if (e != hipSuccess) err.store((int)e);
         if (ev) (void)hipEventDestroy(ev);

@@ -7,16 +7,16 @@
 namespace lbm {
 
 // Copies `bytes` between pageable host memory and the device on `stream`; device `dev`
-// is current. Copies of more than a chunk (4 MiB) are complete on return; smaller
+// is current. Copies of more than 4 MiB are complete on return; smaller
 // ones, those of memory that is not pageable and those into a capture go to hipMemcpyAsync. The runtime's own copy of pageable memory goes through one thread at
-// about 10 GB/s; here worker threads take turns on the stream, each with a pinned buffer of its
+// about 10 GB/s; here worker threads take turns on the stream, each with a pinned 2 MiB of its
 // own, so that one's transfer overlaps the others' copies (and the page faults of a fresh
 // array). 160 x 144 x 128 FP64, density and velocity in and density, velocity and pressure tensor
 // out (330 MB): 27 ms by the runtime's copies, 10 ms so.
 hipError_t copy_pageable(int dev, hipStream_t stream, void *dst, const void *src, size_t bytes, hipMemcpyKind kind);
 
-// The pinned buffers are shared by all contexts of a process, at most 32 MiB; they are freed
-// when the last holder lets go.
+// The pinned buffer is shared by all contexts of a process, 16 MiB; it is freed when the last
+// holder lets go.
 void staging_hold();
 void staging_release();
 

@@ -14,9 +14,9 @@ from tests.gpu_cases import Case
 pytestmark = pytest.mark.gpu
 
 
-# fields of one node more or less than whole 4 MiB chunks, ragged rows (repacked on the device),
-# several chunks per field, a field below one chunk, and a 2D box
-@pytest.mark.parametrize("dims", [(128, 64, 64), (128, 64, 65), (141, 100, 67), (96, 80, 200), (67, 33, 29), (1000, 703, 1)])
+# the largest field copied directly and one plane more, ragged rows (repacked on the device) with a
+# ragged last chunk, more chunks than workers' buffers, a small field, and a 2D box
+@pytest.mark.parametrize("dims", [(128, 64, 64), (128, 64, 65), (141, 100, 67), (96, 80, 300), (67, 33, 29), (1000, 703, 1)])
 def test_fields_of_several_threads_match_the_direct_copy(dims):
     import torch
     import paper_2112_01975_amd as P
