@@ -86,7 +86,9 @@ void staging_release() {
 hipError_t copy_pageable(int dev, hipStream_t stream, void *dst, const void *src, size_t bytes, hipMemcpyKind kind) {
     const int n = (int)std::min<size_t>((size_t)worker_count(), (bytes + kChunk - 1) / kChunk);
     const void *host = kind == hipMemcpyHostToDevice ? src : dst;
-    if (bytes <= kLeast || n < 2 || capturing(stream) || !pageable(host) || !take()) return hipMemcpyAsync(dst, src, bytes, kind, stream);
+    // (hipStreamPerThread names another stream in each worker, not ordered with the caller's)
+    if (bytes <= kLeast || n < 2 || stream == hipStreamPerThread || capturing(stream) || !pageable(host) || !take())
+        return hipMemcpyAsync(dst, src, bytes, kind, stream);
     std::atomic<size_t> next{0};
     std::atomic<int> err{(int)hipSuccess};
     auto work = [&](int w) {

@@ -7,9 +7,9 @@
 namespace lbm {
 
 // Copies `bytes` between pageable host memory and the device on `stream`; device `dev`
-// is current. Copies of more than 4 MiB are complete on return; smaller
-// ones, those of memory that is not pageable and those into a capture go to hipMemcpyAsync. The runtime's own copy of pageable memory goes through one thread at
-// about 10 GB/s; here worker threads take turns on the stream, each with a pinned 2 MiB of its
+// is current. Copies of more than 4 MiB are complete on return; smaller ones, those of memory that
+// is not pageable, those on hipStreamPerThread and those into a capture go to hipMemcpyAsync. The
+// runtime's own copy of pageable memory goes through one thread at about 10 GB/s; here worker threads take turns on the stream, each with a pinned 2 MiB of its
 // own, so that one's transfer overlaps the others' copies (and the page faults of a fresh
 // array). 160 x 144 x 128 FP64, density and velocity in and density, velocity and pressure tensor
 // out (330 MB): 27 ms by the runtime's copies, 10 ms so.

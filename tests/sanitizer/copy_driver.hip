@@ -1,0 +1,128 @@
+// Host-side checks of the copies between pageable memory and the device (csrc/host_copy.hip).
+// The HIP runtime calls it makes are defined here: a copy is a memcpy that notes the calling
+// thread, streams are names, and each thread has its own current device, so no GPU is used.
+// usage: copy_driver CHECK; exits 0 when every expectation of that check holds.
+#include <hip/hip_runtime.h>
+#include <stdio.h>
+#include <string.h>
+
+#include <map>
+#include <mutex>
+#include <string>
+#include <thread>
+#include <vector>
+
+#include "host_copy.hpp"
+
+using namespace lbm;
+
+namespace {
+
+std::mutex mu;
+std::map<std::thread::id, int> copies;   // copies enqueued, by thread
+bool fail_pinned = false;                // pinned allocations fail
+thread_local int device = 0;
+thread_local hipError_t last_error = hipSuccess;
+
+hipError_t note(hipError_t e) {
+    if (e != hipSuccess) last_error = e;
+    return e;
+}
+
+int failures = 0;
+#define EXPECT(cond)                                                                    \
+    do {                                                                                \
+        if (!(cond)) {                                                                  \
+            fprintf(stderr, "expectation failed: %s (line %d)\n", #cond, __LINE__);     \
+            ++failures;                                                                 \
+        }                                                                               \
+    } while (0)
+
+}  // namespace
+
+extern "C" {
+
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode *) { return hipSuccess; }
+hipError_t hipHostMalloc(void **p, size_t bytes, unsigned) {
+    if (fail_pinned) return note(hipErrorOutOfMemory);
+    *p = malloc(bytes);
+    return hipSuccess;
+}
+hipError_t hipHostFree(void *p) {
+    free(p);
+    return hipSuccess;
+}
+hipError_t hipGetLastError() {
+    const hipError_t e = last_error;
+    last_error = hipSuccess;
+    return e;
+}
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t *, const void *) { return note(hipErrorInvalidValue); }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *st) {
+    *st = hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+hipError_t hipGetDevice(int *d) {
+    *d = device;
+    return hipSuccess;
+}
+hipError_t hipSetDevice(int d) {
+    device = d;
+    return hipSuccess;
+}
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) {
+    *e = (hipEvent_t)malloc(1);
+    return hipSuccess;
+}
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e) {
+    free((void *)e);
+    return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipMemcpyAsync(void *dst, const void *src, size_t bytes, hipMemcpyKind, hipStream_t) {
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        ++copies[std::this_thread::get_id()];
+    }
+    memcpy(dst, src, bytes);
+    return hipSuccess;
+}
+
+}  // extern "C"
+
+namespace {
+
+// copies 64 MiB and a ragged end both ways and compares every byte; returns the threads that enqueued
+size_t round_trip(hipStream_t stream) {
+    const size_t n = (size_t(64) << 20) + 12345;
+    std::vector<unsigned char> a(n), b(n), c(n);
+    for (size_t k = 0; k < n; ++k) a[k] = (unsigned char)(k * 2654435761u >> 13);
+    copies.clear();
+    EXPECT(copy_pageable(0, stream, b.data(), a.data(), n, hipMemcpyHostToDevice) == hipSuccess);
+    EXPECT(copy_pageable(0, stream, c.data(), b.data(), n, hipMemcpyDeviceToHost) == hipSuccess);
+    EXPECT(a == c);
+    return copies.size();
+}
+
+}  // namespace
+
+int main(int argc, char **argv) {
+    const std::string check = argc > 1 ? argv[1] : "";
+    staging_hold();
+    if (check == "data") {
+        (void)round_trip((hipStream_t) nullptr);
+    } else if (check == "per_thread_stream") {
+        // that handle names another stream in every thread: only the caller's is the one meant
+        EXPECT(round_trip(hipStreamPerThread) == 1);
+        EXPECT(copies.count(std::this_thread::get_id()) == 1);
+    } else {
+        fprintf(stderr, "unknown check\n");
+        return 2;
+    }
+    staging_release();
+    EXPECT(last_error == hipSuccess);
+    if (!failures) printf("copy driver ok\n");
+    return failures ? 1 : 0;
+}

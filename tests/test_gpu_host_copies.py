@@ -100,3 +100,27 @@ def test_batch_moments_of_small_and_large_cases():
             assert all(np.array_equal(g[2], tot) for g in got[1:])
     finally:
         P.lbm_batch_destroy(b)
+
+
+# the copies are ordered with what the caller queued on its per-thread stream: populations read with
+# steps still queued, and populations set with steps still queued, fields of more than 4 MiB
+def test_copies_are_ordered_on_the_per_thread_stream():
+    import paper_2112_01975_amd as P
+    case = Case(3, 128, 128, 96, a=0.02, T_reduced=0.8)
+    rv, rl = case.coexistence()
+    rho0 = np.random.default_rng(3).uniform(rv, rl, case.N)
+    got = []
+    for handle in (None, 2):   # the context's own stream, hipStreamPerThread
+        with P.Simulation(case.params(check_every=-1)) as s:
+            P.lbm_set_stream(s.ctx, handle)
+            s.init(rho0)
+            first = P.lbm_get_populations(s.ctx)
+            s.step(25)
+            after = P.lbm_get_populations(s.ctx)
+            s.step(25)
+            P.lbm_set_populations(s.ctx, first)
+            s.step(25)
+            got.append((after, P.lbm_get_populations(s.ctx)))
+    assert np.array_equal(got[0][0], got[0][1])
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
