@@ -37,6 +37,20 @@ struct RelaxedCapture {
     ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
 };
 
+// device dev is current while this lives, in the caller's thread too, whose own is then restored
+struct CurrentDevice {
+    int was = -1;
+    hipError_t e;
+    explicit CurrentDevice(int dev) {
+        e = hipGetDevice(&was);
+        if (e == hipSuccess && was != dev) e = hipSetDevice(dev);
+        else was = -1;
+    }
+    ~CurrentDevice() {
+        if (was >= 0) (void)hipSetDevice(was);
+    }
+};
+
 // takes the buffer (allocating it if missing), or returns false
 bool take() {
     RelaxedCapture relaxed;
@@ -94,7 +108,8 @@ hipError_t copy_pageable(int dev, hipStream_t stream, void *dst, const void *src
     auto work = [&](int w) {
         RelaxedCapture relaxed;
         char *const buf = g_buf + (size_t)w * kChunk;
-        hipError_t e = hipSetDevice(dev);
+        const CurrentDevice current(dev);
+        hipError_t e = current.e;
         hipEvent_t ev = nullptr;
         if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
         while (e == hipSuccess && err.load() == (int)hipSuccess) {

@@ -6,8 +6,8 @@
 
 namespace lbm {
 
-// Copies `bytes` between pageable host memory and the device on `stream`; device `dev`
-// is current. Copies of more than 4 MiB are complete on return; smaller ones, those of memory that
+// Copies `bytes` between pageable host memory and device `dev` on `stream`, one of that device.
+// The caller's current device stays as it is. Copies of more than 4 MiB are complete on return; smaller ones, those of memory that
 // is not pageable, those on hipStreamPerThread and those into a capture go to hipMemcpyAsync. The
 // runtime's own copy of pageable memory goes through one thread at about 10 GB/s; here worker threads take turns on the stream, each with a pinned 2 MiB of its
 // own, so that one's transfer overlaps the others' copies (and the page faults of a fresh

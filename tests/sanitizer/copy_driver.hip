@@ -117,6 +117,13 @@ int main(int argc, char **argv) {
         // that handle names another stream in every thread: only the caller's is the one meant
         EXPECT(round_trip(hipStreamPerThread) == 1);
         EXPECT(copies.count(std::this_thread::get_id()) == 1);
+    } else if (check == "current_device") {
+        // the caller's current device is the same afterwards, whichever device is copied to
+        for (int current : {0, 1}) {
+            device = current;
+            (void)round_trip((hipStream_t) nullptr);
+            EXPECT(device == current);
+        }
     } else {
         fprintf(stderr, "unknown check\n");
         return 2;
