@@ -27,6 +27,7 @@
 #include <vector>
 
 #include "../../include/lbm2p.h"
+#include "host_copy.hpp"
 #include "kernels.hpp"
 #include "lattice.hpp"
 #include "runtime_common.hpp"
@@ -458,7 +459,7 @@ struct lbm_batch {
     std::vector<void *> allocs;
     double *partials = nullptr, *io = nullptr, *rscratch = nullptr;
     size_t io_elems = 0;
-    double *pin = nullptr;            // pinned: totals and fields of one case's moments
+    void *pin = nullptr;              // pinned: totals and fields of one case's moments
     hipStream_t stream = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -1038,22 +1039,10 @@ int lbm_batch_moments(lbm_batch *b, int icase, double *rho, double *U, double to
     BHIP(b, hipGetLastError());
     double t[5];
     const size_t last = U ? 8 + N * (1 + (size_t)cd.D) : (rho ? 8 + N : 5);   // doubles of io to bring back
-    if (last <= kPinned / sizeof(double)) {
-        if (!b->pin && hipHostMalloc((void **)&b->pin, kPinned, hipHostMallocDefault) != hipSuccess) {
-            b->pin = nullptr;
-            return bfail(b, LBM_E_NOMEM, "pinned host allocation failed");
-        }
-        BHIP(b, hipMemcpyAsync(b->pin, b->io, last * sizeof(double), hipMemcpyDeviceToHost, b->stream));
-        BHIP(b, hipStreamSynchronize(b->stream));
-        memcpy(t, b->pin, sizeof t);
-        if (rho) memcpy(rho, b->pin + 8, N * sizeof(double));
-        if (U) memcpy(U, b->pin + 8 + N, (size_t)cd.D * N * sizeof(double));
-    } else {
-        BHIP(b, hipMemcpyAsync(t, b->io, sizeof t, hipMemcpyDeviceToHost, b->stream));
-        if (rho) BHIP(b, hipMemcpyAsync(rho, orho, N * sizeof(double), hipMemcpyDeviceToHost, b->stream));
-        if (U) BHIP(b, hipMemcpyAsync(U, oU, (size_t)cd.D * N * sizeof(double), hipMemcpyDeviceToHost, b->stream));
-        BHIP(b, hipStreamSynchronize(b->stream));
-    }
+    const BlockPart parts[] = {{t, 0, sizeof t},
+                               {rho, 8 * sizeof(double), N * sizeof(double)},
+                               {U, (8 + N) * sizeof(double), (size_t)cd.D * N * sizeof(double)}};
+    BHIP(b, read_block(b->stream, b->io, last * sizeof(double), parts, 3, &b->pin, kPinned));
     if (totals) for (int k = 0; k < 4; ++k) totals[k] = t[k];
     return LBM_OK;
 }

@@ -143,4 +143,24 @@ hipError_t copy_pageable(int dev, hipStream_t stream, void *dst, const void *src
     return (hipError_t)err.load();
 }
 
+hipError_t read_block(hipStream_t stream, const void *block, size_t bytes, const BlockPart *parts, int n, void **pin,
+                      size_t pin_bytes) {
+    bool staged = bytes <= pin_bytes;
+    if (staged && !*pin && hipHostMalloc(pin, pin_bytes, hipHostMallocDefault) != hipSuccess) {
+        *pin = nullptr;
+        (void)hipGetLastError();
+        staged = false;
+    }
+    hipError_t e = hipSuccess;
+    if (staged) e = hipMemcpyAsync(*pin, block, bytes, hipMemcpyDeviceToHost, stream);
+    for (int k = 0; k < n && !staged && e == hipSuccess; ++k)
+        if (parts[k].dst)
+            e = hipMemcpyAsync(parts[k].dst, (const char *)block + parts[k].at, parts[k].bytes, hipMemcpyDeviceToHost, stream);
+    const hipError_t se = hipStreamSynchronize(stream);
+    if (e == hipSuccess) e = se;
+    for (int k = 0; k < n && staged && e == hipSuccess; ++k)
+        if (parts[k].dst) memcpy(parts[k].dst, (const char *)*pin + parts[k].at, parts[k].bytes);
+    return e;
+}
+
 }  // namespace lbm

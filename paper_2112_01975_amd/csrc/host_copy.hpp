@@ -20,4 +20,15 @@ hipError_t copy_pageable(int dev, hipStream_t stream, void *dst, const void *src
 void staging_hold();
 void staging_release();
 
+// Reads parts of one device block back and waits for them. A block of up to pin_bytes comes in one
+// copy into pinned memory at *pin (allocated when it is null; the caller frees it with hipHostFree)
+// and is handed out from there; without that memory, and for larger blocks, each part is copied
+// directly.
+struct BlockPart {
+    void *dst;          // nullptr: not wanted
+    size_t at, bytes;   // its place in the block
+};
+hipError_t read_block(hipStream_t stream, const void *block, size_t bytes, const BlockPart *parts, int n, void **pin,
+                      size_t pin_bytes);
+
 }  // namespace lbm

@@ -106,6 +106,18 @@ size_t round_trip(hipStream_t stream) {
     return copies.size();
 }
 
+// two parts of a block of 1000 bytes, with and without pinned memory of pin_bytes; returns the copies made
+int read_parts(size_t pin_bytes, void **pin) {
+    std::vector<char> block(1000);
+    for (size_t k = 0; k < block.size(); ++k) block[k] = (char)(k * 7);
+    std::vector<char> a(40, 'x'), b(600, 'x');
+    const BlockPart parts[] = {{a.data(), 0, a.size()}, {nullptr, 40, 360}, {b.data(), 400, b.size()}};
+    copies.clear();
+    EXPECT(read_block((hipStream_t) nullptr, block.data(), block.size(), parts, 3, pin, pin_bytes) == hipSuccess);
+    EXPECT(!memcmp(a.data(), block.data(), a.size()) && !memcmp(b.data(), block.data() + 400, b.size()));
+    return copies[std::this_thread::get_id()];
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -124,6 +136,18 @@ int main(int argc, char **argv) {
             (void)round_trip((hipStream_t) nullptr);
             EXPECT(device == current);
         }
+    } else if (check == "block") {
+        void *pin = nullptr;
+        EXPECT(read_parts(999, &pin) == 2 && !pin);    // larger than the pinned memory: part by part
+        EXPECT(read_parts(1000, &pin) == 1 && pin);
+        EXPECT(read_parts(1000, &pin) == 1);
+        (void)hipHostFree(pin);
+    } else if (check == "no_pinned_memory") {
+        // everything is copied directly, and no error is left behind
+        fail_pinned = true;
+        void *pin = nullptr;
+        EXPECT(read_parts(1 << 20, &pin) == 2 && !pin);
+        EXPECT(round_trip((hipStream_t) nullptr) == 1);
     } else {
         fprintf(stderr, "unknown check\n");
         return 2;
