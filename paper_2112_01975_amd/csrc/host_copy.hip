@@ -51,16 +51,20 @@ struct CurrentDevice {
     }
 };
 
+// pinned memory, or nullptr with no error left behind
+void *pinned(size_t bytes) {
+    RelaxedCapture relaxed;
+    void *p = nullptr;
+    if (hipHostMalloc(&p, bytes, hipHostMallocPortable) == hipSuccess) return p;
+    (void)hipGetLastError();
+    return nullptr;
+}
+
 // takes the buffer (allocating it if missing), or returns false
 bool take() {
-    RelaxedCapture relaxed;
     std::lock_guard<std::mutex> lk(g_mu);
     if (g_busy || g_holders == 0) return false;
-    if (!g_buf && hipHostMalloc((void **)&g_buf, kWorkers * kChunk, hipHostMallocPortable) != hipSuccess) {
-        g_buf = nullptr;
-        (void)hipGetLastError();
-        return false;
-    }
+    if (!g_buf && !(g_buf = (char *)pinned(kWorkers * kChunk))) return false;
     g_busy = true;
     return true;
 }
@@ -146,11 +150,7 @@ hipError_t copy_pageable(int dev, hipStream_t stream, void *dst, const void *src
 hipError_t read_block(hipStream_t stream, const void *block, size_t bytes, const BlockPart *parts, int n, void **pin,
                       size_t pin_bytes) {
     bool staged = bytes <= pin_bytes;
-    if (staged && !*pin && hipHostMalloc(pin, pin_bytes, hipHostMallocDefault) != hipSuccess) {
-        *pin = nullptr;
-        (void)hipGetLastError();
-        staged = false;
-    }
+    if (staged && !*pin) staged = (*pin = pinned(pin_bytes)) != nullptr;
     hipError_t e = hipSuccess;
     if (staged) e = hipMemcpyAsync(*pin, block, bytes, hipMemcpyDeviceToHost, stream);
     for (int k = 0; k < n && !staged && e == hipSuccess; ++k)

@@ -21,6 +21,8 @@ namespace {
 std::mutex mu;
 std::map<std::thread::id, int> copies;   // copies enqueued, by thread
 bool fail_pinned = false;                // pinned allocations fail
+int strict_allocations = 0;              // those made while a capture on another thread would break
+thread_local hipStreamCaptureMode capture_mode = hipStreamCaptureModeGlobal;
 thread_local int device = 0;
 thread_local hipError_t last_error = hipSuccess;
 
@@ -42,8 +44,12 @@ int failures = 0;
 
 extern "C" {
 
-hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode *) { return hipSuccess; }
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode *mode) {
+    std::swap(*mode, capture_mode);
+    return hipSuccess;
+}
 hipError_t hipHostMalloc(void **p, size_t bytes, unsigned) {
+    strict_allocations += capture_mode != hipStreamCaptureModeRelaxed;
     if (fail_pinned) return note(hipErrorOutOfMemory);
     *p = malloc(bytes);
     return hipSuccess;
@@ -148,6 +154,13 @@ int main(int argc, char **argv) {
         void *pin = nullptr;
         EXPECT(read_parts(1 << 20, &pin) == 2 && !pin);
         EXPECT(round_trip((hipStream_t) nullptr) == 1);
+    } else if (check == "capture_mode") {
+        // pinned memory is allocated in the relaxed capture mode, the thread's own is restored
+        void *pin = nullptr;
+        (void)read_parts(1000, &pin);
+        (void)hipHostFree(pin);
+        (void)round_trip((hipStream_t) nullptr);
+        EXPECT(strict_allocations == 0 && capture_mode == hipStreamCaptureModeGlobal);
     } else {
         fprintf(stderr, "unknown check\n");
         return 2;
