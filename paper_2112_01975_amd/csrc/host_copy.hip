@@ -150,6 +150,7 @@ hipError_t copy_pageable(int dev, hipStream_t stream, void *dst, const void *src
 hipError_t read_block(hipStream_t stream, const void *block, size_t bytes, const BlockPart *parts, int n, void **pin,
                       size_t pin_bytes) {
     bool staged = bytes <= pin_bytes;
+    for (int k = 0; k < n; ++k) staged = staged && (!parts[k].dst || pageable(parts[k].dst));
     if (staged && !*pin) staged = (*pin = pinned(pin_bytes)) != nullptr;
     hipError_t e = hipSuccess;
     if (staged) e = hipMemcpyAsync(*pin, block, bytes, hipMemcpyDeviceToHost, stream);

@@ -22,8 +22,8 @@ void staging_release();
 
 // Reads parts of one device block back and waits for them. A block of up to pin_bytes comes in one
 // copy into pinned memory at *pin (allocated when it is null; the caller frees it with hipHostFree)
-// and is handed out from there; without that memory, and for larger blocks, each part is copied
-// directly.
+// and is handed out from there. Without that memory, for larger blocks, and where a part goes to
+// device, managed or pinned memory, each part is copied directly.
 struct BlockPart {
     void *dst;          // nullptr: not wanted
     size_t at, bytes;   // its place in the block

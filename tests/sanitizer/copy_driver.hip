@@ -21,6 +21,7 @@ namespace {
 std::mutex mu;
 std::map<std::thread::id, int> copies;   // copies enqueued, by thread
 bool fail_pinned = false;                // pinned allocations fail
+const void *device_memory = nullptr;     // an address that is device memory; all others are pageable
 int strict_allocations = 0;              // those made while a capture on another thread would break
 thread_local hipStreamCaptureMode capture_mode = hipStreamCaptureModeGlobal;
 thread_local int device = 0;
@@ -63,7 +64,11 @@ hipError_t hipGetLastError() {
     last_error = hipSuccess;
     return e;
 }
-hipError_t hipPointerGetAttributes(hipPointerAttribute_t *, const void *) { return note(hipErrorInvalidValue); }
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *p) {
+    if (p != device_memory) return note(hipErrorInvalidValue);
+    a->type = hipMemoryTypeDevice;
+    return hipSuccess;
+}
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *st) {
     *st = hipStreamCaptureStatusNone;
     return hipSuccess;
@@ -113,11 +118,12 @@ size_t round_trip(hipStream_t stream) {
 }
 
 // two parts of a block of 1000 bytes, with and without pinned memory of pin_bytes; returns the copies made
-int read_parts(size_t pin_bytes, void **pin) {
+int read_parts(size_t pin_bytes, void **pin, bool to_device = false) {
     std::vector<char> block(1000);
     for (size_t k = 0; k < block.size(); ++k) block[k] = (char)(k * 7);
     std::vector<char> a(40, 'x'), b(600, 'x');
     const BlockPart parts[] = {{a.data(), 0, a.size()}, {nullptr, 40, 360}, {b.data(), 400, b.size()}};
+    device_memory = to_device ? b.data() : nullptr;
     copies.clear();
     EXPECT(read_block((hipStream_t) nullptr, block.data(), block.size(), parts, 3, pin, pin_bytes) == hipSuccess);
     EXPECT(!memcmp(a.data(), block.data(), a.size()) && !memcmp(b.data(), block.data() + 400, b.size()));
@@ -147,6 +153,11 @@ int main(int argc, char **argv) {
         EXPECT(read_parts(999, &pin) == 2 && !pin);    // larger than the pinned memory: part by part
         EXPECT(read_parts(1000, &pin) == 1 && pin);
         EXPECT(read_parts(1000, &pin) == 1);
+        (void)hipHostFree(pin);
+    } else if (check == "block_to_device") {
+        // the host does not write to device memory: part by part
+        void *pin = nullptr;
+        EXPECT(read_parts(1000, &pin, true) == 2);
         (void)hipHostFree(pin);
     } else if (check == "no_pinned_memory") {
         // everything is copied directly, and no error is left behind

@@ -124,3 +124,30 @@ def test_copies_are_ordered_on_the_per_thread_stream():
     assert np.array_equal(got[0][0], got[0][1])
     for a, b in zip(*got):
         assert np.array_equal(a, b)
+
+
+# device and pinned arrays get the same values as pageable ones, for small cases and large
+def test_batch_moments_into_device_and_pinned_arrays():
+    import ctypes as C
+    import torch
+    import paper_2112_01975_amd as P
+    cases = [Case(2, 64, 48, a=0.02, T_reduced=0.8), Case(2, 256, 192, a=0.02, T_reduced=0.8)]
+    rv, rl = cases[0].coexistence()
+    rng = np.random.default_rng(12)
+    b = P.lbm_batch_create([c.params() for c in cases])
+    try:
+        for k, c in enumerate(cases):
+            P.lbm_batch_init_fields(b, k, rng.uniform(rv, rl, c.N))
+        for k, c in enumerate(cases):
+            rho, U, tot = np.empty(c.N), np.empty((2, c.N)), np.empty(4)
+            ptr = [x.ctypes.data_as(C.c_void_p) for x in (rho, U, tot)]
+            assert P.lib().lbm_batch_moments(b, k, *ptr) == 0
+            for mem in (torch.zeros(3 * c.N, dtype=torch.float64, device="cuda"),
+                        torch.zeros(3 * c.N, dtype=torch.float64, pin_memory=True)):
+                torch.cuda.synchronize()
+                at, t = mem.data_ptr(), np.empty(4)
+                assert P.lib().lbm_batch_moments(b, k, C.c_void_p(at), C.c_void_p(at + 8 * c.N), t.ctypes.data_as(C.c_void_p)) == 0
+                got = mem.cpu().numpy()
+                assert np.array_equal(got[:c.N], rho) and np.array_equal(got[c.N:], U.ravel()) and np.array_equal(t, tot)
+    finally:
+        P.lbm_batch_destroy(b)
