@@ -333,14 +333,13 @@ void launch_single(hipStream_t s, const void *A, void *B, const Geom &g, const u
 
 template <class S, class C, bool MASK>
 D2Launch pick(int threads, int per) {
-    switch (threads * 8 + per) {
-    case SX * SY * 8: return launch_single<S, C, MASK>;
-    case 256 * 8 + 1: return launch<S, C, MASK, 256, 1>;
-    case 512 * 8 + 2: return launch<S, C, MASK, 512, 2>;
-    case 512 * 8 + 3: return launch<S, C, MASK, 512, 3>;
-    case 1024 * 8 + 2: if constexpr (sizeof(C) == 4) return launch<S, C, MASK, 1024, 2>; else return nullptr;   // 128 registers
-    default: return nullptr;
-    }
+    if (threads == SX * SY && per == 0) return launch_single<S, C, MASK>;
+    if (threads == 256 && per == 1) return launch<S, C, MASK, 256, 1>;
+    if (threads == 512 && per == 2) return launch<S, C, MASK, 512, 2>;
+    if (threads == 512 && per == 3) return launch<S, C, MASK, 512, 3>;
+    if constexpr (sizeof(C) == 4)   // FP64 does not fit the 128 registers of 1024 threads
+        if (threads == 1024 && per == 2) return launch<S, C, MASK, 1024, 2>;
+    return nullptr;
 }
 
 }  // namespace

@@ -332,7 +332,8 @@ int env_int(const char *name, int dflt) {
 // node is faster. Measured us per step: this choice | one thread per node of 64 x 8 tiles:
 //   FP64  64^2 2.6 | 5.0   256^2 4.0 | 5.3   400x380 5.9 | 7.1   512^2 10.5 | 9.8   2040x1900 126 | 121
 //   FP32  64^2 2.2 | 4.0   256^2 3.0 | 4.2   512^2 5.1 | 5.7     1000x900 16.8 | 19     2048^2 63 | 68
-// LBM2P_TILE="threads,nodes per thread,width,height,steps" overrides ("512,0,64,8,1": one thread per node).
+// LBM2P_TILE="threads,nodes per thread,width,height,steps" overrides ("512,0,64,8,1": one thread per node);
+// one that does not fit or has no kernel is ignored.
 void plan_tiles(lbm_ctx *c, int cus) {
     static constexpr int shapes[][2] = {{256, 1}, {512, 2}, {512, 3}, {1024, 2}};
     const int size = c->fp64 ? 8 : 4;

@@ -171,3 +171,22 @@ def test_profile_summaries_from_counter_files(tmp_path):
     out = profsum.counters("k_fused3", 256, 8, [str(c)], "cmd")
     assert "TA_BUSY_avr_frac_of_active_cycles: 0.7500" in out
     assert "TD_TD_BUSY_sum_frac_of_active_cycles: 0.6875" in out
+
+
+def test_d2q9_kernels_are_found_by_their_exact_workgroup_shape():
+    # (threads, nodes per thread) of every compiled shape, and no other pair of the same key
+    import paper_2112_01975_amd as P
+
+    class Shape(ctypes.Structure):
+        _fields_ = [(n, ctypes.c_int) for n in ("threads", "per", "tx", "ty", "steps")]
+
+    find = ctypes.CDLL(P.lbm.LIB_PATH)._ZN3lbm11d2_launcherEbbRKNS_7D2ShapeE
+    find.restype = ctypes.c_void_p
+    find.argtypes = [ctypes.c_bool, ctypes.c_bool, ctypes.POINTER(Shape)]
+    for fp64 in (False, True):
+        shapes = {(512, 0), (256, 1), (512, 2), (512, 3)} | (set() if fp64 else {(1024, 2)})
+        for masked in (False, True):
+            for threads in range(0, 1101):
+                for per in range(-1, 20):
+                    got = find(fp64, masked, Shape(threads, per, 64, 8, 1))
+                    assert bool(got) == ((threads, per) in shapes), (fp64, masked, threads, per)
