@@ -71,9 +71,17 @@ template <int D, class S, class C> struct GlobalView {
     }
     __device__ __forceinline__ bool solid(int n) const { return mask && mask[n]; }
     __device__ __forceinline__ int global_index(int n) const { return n; }
+    // arrays past 4 GiB (far_arrays): of the cases a batch accepts only FP64 D2Q9 can have them
+    __device__ __forceinline__ bool far() const {
+        return D == 2 && sizeof(S) == 8 && (unsigned long long)g.N * sizeof(S) > (1ull << 32);
+    }
+    template <class Ix> __device__ __forceinline__ void gather_as(const Node &nd, int n, C (&h)[Lat<D>::Q]) const {
+        if (mask) gather<D, S, C, true, Ix>(A, g.qs, mask, nd.nb, n, h);
+        else gather<D, S, C, false, Ix>(A, g.qs, mask, nd.nb, n, h);
+    }
     __device__ __forceinline__ void gather_at(const Node &nd, int n, C (&h)[Lat<D>::Q]) const {
-        if (mask) gather<D, S, C, true>(A, g.qs, mask, nd.nb, n, h);
-        else gather<D, S, C, false>(A, g.qs, mask, nd.nb, n, h);
+        if (far()) gather_as<size_t>(nd, n, h);
+        else gather_as<unsigned>(nd, n, h);
     }
     __device__ __forceinline__ int at1(const Node &nd, int cx, int cy, int cz) const { return nd.nb.at(cx, cy, cz); }
     __device__ __forceinline__ int at2(const Node &nd, int cx, int cy, int cz) const {
@@ -84,7 +92,10 @@ template <int D, class S, class C> struct GlobalView {
     __device__ __forceinline__ C &rho(int n) const { return frho[n]; }
     __device__ __forceinline__ C &psi(int n) const { return fpsi[n]; }
     __device__ __forceinline__ C &gfield(int a, int n) const { return fg[a * g.N + n]; }
-    __device__ __forceinline__ void store(int i, int n, C v) const { st_at(B + i * g.qs, (unsigned)n, S(v)); }
+    __device__ __forceinline__ void store(int i, int n, C v) const {
+        if (far()) st_at(B + i * g.qs, (size_t)n, S(v));
+        else st_at(B + i * g.qs, (unsigned)n, S(v));
+    }
 };
 
 // phase 1 at node n (view coordinates nd): rho, signed psi and g = rho u^3 of the current
@@ -745,7 +756,7 @@ int lbm_batch_create(const lbm_params *cases, int ncases, lbm_batch **out) {
         }
         b->params[c].mask = nullptr;
         b->params[c].rho_wall_field = nullptr;
-        b->ks[c] = kernel_set(cd.D, cd.fp64, cd.mask != nullptr);
+        b->ks[c] = kernel_set(cd.D, cd.fp64, cd.mask != nullptr, far_arrays(cd.g, cd.fp64));
         if (cd.mask) b->ks[c].links(b->stream, cd.mask, cd.links, cd.g);
         b->nblk[c] = moment_block_count(cd.D, cd.g);
         max_nblk = std::max(max_nblk, b->nblk[c]);

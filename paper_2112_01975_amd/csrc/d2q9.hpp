@@ -44,4 +44,7 @@ using D2Launch = void (*)(hipStream_t, const void *A, void *B, const Geom &, con
 // kernel of a workgroup shape; nullptr when there is none
 D2Launch d2_launcher(bool fp64, bool masked, const D2Shape &sh);
 
+// the kernel with a thread per tile node for far_arrays, which the tiles do not address
+D2Launch d2_far_launcher(bool fp64, bool masked);
+
 }  // namespace lbm

@@ -240,7 +240,7 @@ __global__ __launch_bounds__(NT) void k_d2q9(const S *__restrict__ A, S *__restr
 // recomputed halo costs more there than the launches and traffic they save: 2040x1900 FP64 121 us
 // a step, 4.6 TB/s of populations against 5.4 for a copy, and 126 in tiles.
 constexpr int SX = 64, SY = 8, SHALO = 2;
-template <class S, class C, bool MASK>
+template <class S, class C, bool MASK, class Ix>
 __global__ __launch_bounds__(SX *SY) void k_d2q9_single(const S *__restrict__ A, S *__restrict__ B, Geom g,
                                                         const uint32_t *__restrict__ links, Params<C> p, D2Tiles tl) {
     constexpr int LX = SX + 2 * SHALO, LY = SY + 2 * SHALO, LS = LX * LY, NTH = SX * SY, NH = LS - NTH;
@@ -272,8 +272,8 @@ __global__ __launch_bounds__(SX *SY) void k_d2q9_single(const S *__restrict__ A,
     const int on = ox + g.px * oy, hn = hx + g.px * hy;
     const uint32_t olm = MASK ? links[on] : 0u, hlm = MASK && has_halo ? links[hn] : 0u;
     C h[9], hh[9];
-    if (!link_solid(olm)) gather_links<2, S, C, MASK>(A, g.qs, olm, Nbr<2>(g, ox, oy, 0), on, h, p.link_q);
-    if (has_halo && !link_solid(hlm)) gather_links<2, S, C, MASK>(A, g.qs, hlm, Nbr<2>(g, hx, hy, 0), hn, hh, p.link_q);
+    if (!link_solid(olm)) gather_links<2, S, C, MASK, Ix>(A, g.qs, olm, Nbr<2>(g, ox, oy, 0), on, h, p.link_q);
+    if (has_halo && !link_solid(hlm)) gather_links<2, S, C, MASK, Ix>(A, g.qs, hlm, Nbr<2>(g, hx, hy, 0), hn, hh, p.link_q);
     C drho = C(0), rinv = C(0), spsi = C(0), jj[2] = {C(0), C(0)};
     auto stage = [&](int at, int n, uint32_t lm, const C (&hs)[9], bool own) __attribute__((always_inline)) {
         C rho, ga[2] = {C(0), C(0)};
@@ -306,7 +306,7 @@ __global__ __launch_bounds__(SX *SY) void k_d2q9_single(const S *__restrict__ A,
     update_node<C>(p, gw, s_rp + e, s_gx + e, s_gy + e, LX, p.rho_ref, p.accel[0], p.accel[1], drho, rinv, spsi, jj, h);
     static_for<0, 9>([&](auto I) {
         constexpr int i = decltype(I)::value;
-        st_nt_at(B + i * g.qs, (unsigned)(x + g.px * y), S(h[i]));
+        st_nt_at(B + i * g.qs, (Ix)(x + g.px * y), S(h[i]));
     });
 }
 
@@ -324,16 +324,16 @@ void launch(hipStream_t s, const void *A, void *B, const Geom &g, const uint32_t
                        (const S *)A, (S *)B, g, links, *(const Params<C> *)prm, t);
 }
 
-template <class S, class C, bool MASK>
+template <class S, class C, bool MASK, class Ix>
 void launch_single(hipStream_t s, const void *A, void *B, const Geom &g, const uint32_t *links, const void *prm,
                    const D2Tiles &t) {
-    hipLaunchKernelGGL((k_d2q9_single<S, C, MASK>), dim3(blocks(t)), dim3(SX * SY), 0, s, (const S *)A, (S *)B, g, links,
+    hipLaunchKernelGGL((k_d2q9_single<S, C, MASK, Ix>), dim3(blocks(t)), dim3(SX * SY), 0, s, (const S *)A, (S *)B, g, links,
                        *(const Params<C> *)prm, t);
 }
 
 template <class S, class C, bool MASK>
 D2Launch pick(int threads, int per) {
-    if (threads == SX * SY && per == 0) return launch_single<S, C, MASK>;
+    if (threads == SX * SY && per == 0) return launch_single<S, C, MASK, unsigned>;
     if (threads == 256 && per == 1) return launch<S, C, MASK, 256, 1>;
     if (threads == 512 && per == 2) return launch<S, C, MASK, 512, 2>;
     if (threads == 512 && per == 3) return launch<S, C, MASK, 512, 3>;
@@ -371,6 +371,11 @@ bool d2_fits(bool fp64, const D2Shape &sh) {
     const int m = 2 + 3 * (sh.steps - 1), w = sh.tx + 2 * m, h = sh.ty + 2 * m;
     return w * h <= d2_fields(sh.threads, sh.per) && (sh.steps == 1 || (w - 4) * (h - 4) <= d2_pops(sh.threads, sh.per)) &&
            d2_tiles(Geom{1, 1, 1, 1, 1, 1}, fp64, sh, sh.steps).lds <= 160 * 1024;
+}
+
+D2Launch d2_far_launcher(bool fp64, bool masked) {
+    if (fp64) return masked ? launch_single<double, double, true, size_t> : launch_single<double, double, false, size_t>;
+    return masked ? launch_single<float, float, true, size_t> : launch_single<float, float, false, size_t>;
 }
 
 D2Launch d2_launcher(bool fp64, bool masked, const D2Shape &sh) {

@@ -70,7 +70,12 @@ struct KernelSet {
     int moment_blocks;  // filled by kernel_blocks()
 };
 
-KernelSet kernel_set(int D, bool fp64, bool masked);
+// whether a population array reaches past 4 GiB, the range of a 32-bit byte offset
+bool far_arrays(const Geom &g, bool fp64);
+
+// far: for such arrays
+KernelSet kernel_set(int D, bool fp64, bool masked, bool far);
+
 int moment_block_count(int D, const Geom &g);
 
 // deterministic FP64 tree over n partial rows of kPartialSlots values -> totals[0..4]: levels

@@ -339,7 +339,8 @@ void plan_tiles(lbm_ctx *c, int cus) {
     const int size = c->fp64 ? 8 : 4;
     D2Shape best{512, 0, 64, 8, 1};
     double least = -1.0;
-    if (!(c->fp64 && (double)c->g.nx * c->g.ny > 200e3))
+    const bool far = far_arrays(c->g, c->fp64);
+    if (!far && !(c->fp64 && (double)c->g.nx * c->g.ny > 200e3))
         for (const auto &wg : shapes)
             for (int tx = 8; tx <= 64; tx += 8)
                 for (int ty = 4; ty <= 32; ty += 4)
@@ -364,12 +365,12 @@ void plan_tiles(lbm_ctx *c, int cus) {
                     }
     const char *e = getenv("LBM2P_TILE");
     D2Shape w{};
-    if (e && sscanf(e, "%d,%d,%d,%d,%d", &w.threads, &w.per, &w.tx, &w.ty, &w.steps) == 5 && d2_fits(c->fp64, w) &&
+    if (!far && e && sscanf(e, "%d,%d,%d,%d,%d", &w.threads, &w.per, &w.tx, &w.ty, &w.steps) == 5 && d2_fits(c->fp64, w) &&
         d2_launcher(c->fp64, c->masked, w))
         best = w;
     c->tile_steps = best.steps;
     for (int k = 1; k <= best.steps; ++k) c->tiles[k - 1] = d2_tiles(c->g, c->fp64, best, k);
-    c->d2 = d2_launcher(c->fp64, c->masked, best);
+    c->d2 = far ? d2_far_launcher(c->fp64, c->masked) : d2_launcher(c->fp64, c->masked, best);
 }
 
 }  // namespace
@@ -406,7 +407,7 @@ int lbm_create(const lbm_params *p, lbm_ctx **out) {
     }
     fill_params(p, &c->pd);
     fill_params(p, &c->pf);
-    c->ks = kernel_set(c->D, c->fp64, c->masked);
+    c->ks = kernel_set(c->D, c->fp64, c->masked, far_arrays(c->g, c->fp64));
     c->nblk = moment_block_count(c->D, c->g);
     // single-pass z-march for D3Q27 (LBM2P_TWO_PASS=1 forces the two-pass step;
     // LBM2P_FUSED_TX / _TY / _TZ override the tile shape and z-chunk length). By default

@@ -65,18 +65,18 @@ template <int D> struct Nbr {
 
 // Element idx of the array that starts at `base`, addressed as a uniform 64-bit base plus
 // a 32-bit byte offset: the compiler then issues global loads/stores with an SGPR base
-// and one VGPR offset (saddr form) instead of a 64-bit address per lane. Every
-// population array is smaller than 4 GiB (checked when a context is created).
-template <class T> __device__ __forceinline__ T ld_at(const T *__restrict__ base, unsigned idx) {
-    return *(const T *)((const char *)base + idx * (unsigned)sizeof(T));
+// and one VGPR offset (saddr form) instead of a 64-bit address per lane. Arrays of more than
+// 4 GiB (far_arrays) take Ix = size_t, with 64-bit offsets.
+template <class Ix = unsigned, class T> __device__ __forceinline__ T ld_at(const T *__restrict__ base, Ix idx) {
+    return *(const T *)((const char *)base + idx * (Ix)sizeof(T));
 }
-template <class T> __device__ __forceinline__ void st_at(T *__restrict__ base, unsigned idx, T v) {
-    *(T *)((char *)base + idx * (unsigned)sizeof(T)) = v;
+template <class Ix = unsigned, class T> __device__ __forceinline__ void st_at(T *__restrict__ base, Ix idx, T v) {
+    *(T *)((char *)base + idx * (Ix)sizeof(T)) = v;
 }
 // The same store with the non-temporal cache policy, for a lattice that the step writing it
 // does not read again (its lines then do not displace the ones being read from L2).
-template <class T> __device__ __forceinline__ void st_nt_at(T *__restrict__ base, unsigned idx, T v) {
-    __builtin_nontemporal_store(v, (T *)((char *)base + idx * (unsigned)sizeof(T)));
+template <class Ix = unsigned, class T> __device__ __forceinline__ void st_nt_at(T *__restrict__ base, Ix idx, T v) {
+    __builtin_nontemporal_store(v, (T *)((char *)base + idx * (Ix)sizeof(T)));
 }
 
 // Solid-neighbour bits of a node (one word per node, built once per geometry): bit i is set
@@ -103,16 +103,16 @@ __device__ __forceinline__ C wall_mix(C q, C back, bool ahead_solid, C ahead, C 
 // every pull one load at a selected address: a mask byte per source node cost as many loads
 // again, each before a branch (512x256x256 with pillars, FP32: moment pass 1.30 ms so, 0.83
 // with the links).
-template <int D, class S, class C, bool MASK>
+template <int D, class S, class C, bool MASK, class Ix = unsigned>
 __device__ __forceinline__ void gather_links(const S *__restrict__ A, long long qs, uint32_t lm, const Nbr<D> &nb, int n,
                                              C (&h)[Lat<D>::Q], const C *__restrict__ lq) {
     static_for<0, Lat<D>::Q>([&](auto I) {
         constexpr int i = decltype(I)::value;
         constexpr int cx = Lat<D>::c(i, 0), cy = Lat<D>::c(i, 1), cz = Lat<D>::c(i, 2);
         if constexpr (i == 0) {
-            h[0] = C(ld_at(A, (unsigned)n));
+            h[0] = C(ld_at(A, (Ix)n));
         } else if constexpr (!MASK) {
-            h[i] = C(ld_at(A + i * qs, (unsigned)nb.at(-cx, -cy, -cz)));
+            h[i] = C(ld_at(A + i * qs, (Ix)nb.at(-cx, -cy, -cz)));
         } else {
             const bool w = (lm >> i) & 1u;
             const S *a = A + (w ? opp<D>(i) * qs : i * qs) + (w ? n : nb.at(-cx, -cy, -cz));
@@ -124,25 +124,25 @@ __device__ __forceinline__ void gather_links(const S *__restrict__ A, long long 
             constexpr int i = decltype(I)::value;
             constexpr int o = opp<D>(i);   // the fraction of the link n -> n - c_i is stored under opp(i)
             if ((lm >> i) & 1u)
-                h[i] = wall_mix<C>(ld_at(lq + o * qs, (unsigned)n), h[i], (lm >> o) & 1u,
-                                   C(ld_at(A + o * qs, (unsigned)nb.at(Lat<D>::c(i, 0), Lat<D>::c(i, 1), Lat<D>::c(i, 2)))),
-                                   C(ld_at(A + i * qs, (unsigned)n)));
+                h[i] = wall_mix<C>(ld_at(lq + o * qs, (Ix)n), h[i], (lm >> o) & 1u,
+                                   C(ld_at(A + o * qs, (Ix)nb.at(Lat<D>::c(i, 0), Lat<D>::c(i, 1), Lat<D>::c(i, 2)))),
+                                   C(ld_at(A + i * qs, (Ix)n)));
         });
 }
 
 // The same pull with the solid flags of a mask and halfway walls (the batched sweep).
-template <int D, class S, class C, bool MASK>
+template <int D, class S, class C, bool MASK, class Ix = unsigned>
 __device__ __forceinline__ void gather(const S *__restrict__ A, long long qs, const uint8_t *__restrict__ mask,
                                        const Nbr<D> &nb, int n, C (&h)[Lat<D>::Q]) {
     static_for<0, Lat<D>::Q>([&](auto I) {
         constexpr int i = decltype(I)::value;
         constexpr int cx = Lat<D>::c(i, 0), cy = Lat<D>::c(i, 1), cz = Lat<D>::c(i, 2);
         if constexpr (i == 0) {
-            h[0] = C(ld_at(A, (unsigned)n));
+            h[0] = C(ld_at(A, (Ix)n));
         } else {
-            const unsigned s = (unsigned)nb.at(-cx, -cy, -cz);
+            const Ix s = (Ix)nb.at(-cx, -cy, -cz);
             if constexpr (MASK) {
-                h[i] = ld_at(mask, s) ? C(ld_at(A + opp<D>(i) * qs, (unsigned)n)) : C(ld_at(A + i * qs, s));
+                h[i] = ld_at(mask, s) ? C(ld_at(A + opp<D>(i) * qs, (Ix)n)) : C(ld_at(A + i * qs, s));
             } else {
                 h[i] = C(ld_at(A + i * qs, s));
             }

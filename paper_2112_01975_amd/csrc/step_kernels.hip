@@ -58,7 +58,7 @@ __device__ __forceinline__ void block_sum5(double (&v)[kPartialSlots], double *_
 // Moment pass. Only what the caller uses is written: the two-pass step and the pressure tensor
 // take rho (and g) in the pitched layout, the output of fields rho and the bare velocity in
 // the user layout, a watchdog check the partials alone.
-template <int D, class S, class C, bool MASK>
+template <int D, class S, class C, bool MASK, class Ix>
 __global__ __launch_bounds__(256) void k_moments(const S *__restrict__ A, Geom g, const uint32_t *__restrict__ links,
                                                  Params<C> p, C *__restrict__ rho_out, C *__restrict__ gf,
                                                  double *__restrict__ out_rho, double *__restrict__ out_U,
@@ -75,7 +75,7 @@ __global__ __launch_bounds__(256) void k_moments(const S *__restrict__ A, Geom g
         } else {
             Nbr<D> nb(g, x, y, z);
             C h[Lat<D>::Q];
-            gather_links<D, S, C, MASK>(A, g.qs, lm, nb, n, h, p.link_q);
+            gather_links<D, S, C, MASK, Ix>(A, g.qs, lm, nb, n, h, p.link_q);
             C sum, j[3];
             moments_of<D, C>(h, sum, j);
             rho = p.rho_ref + sum;
@@ -140,7 +140,7 @@ enum { MODE_STEP = 0, MODE_VEL = 1, MODE_INIT = 2, MODE_PT = 3 };
 //            momentum flux of the pulled (pre-collision) populations minus the one- and
 //            two-ring pseudo-potential and capillary tensors, which enter with the sign of
 //            the momentum source S = -F.
-template <int D, class S, class C, bool MASK, int MODE>
+template <int D, class S, class C, bool MASK, int MODE, class Ix = unsigned>
 __global__ __launch_bounds__(TX *TY) void k_collide(
     const S *__restrict__ A, S *__restrict__ B, Geom g, const uint8_t *__restrict__ mask,
     const uint32_t *__restrict__ links, Params<C> p, const C *__restrict__ rho_f, const C *__restrict__ gf,
@@ -178,7 +178,7 @@ __global__ __launch_bounds__(TX *TY) void k_collide(
         if constexpr (MODE == MODE_PT) {
             Nbr<D> nb(g, x, y, z);
             C h[Lat<D>::Q];
-            gather_links<D, S, C, MASK>(A, g.qs, lm, nb, n, h, p.link_q);
+            gather_links<D, S, C, MASK, Ix>(A, g.qs, lm, nb, n, h, p.link_q);
             constexpr int NC = D * (D + 1) / 2;
             constexpr int ca[6] = {0, 1, D == 3 ? 2 : 0, 0, 0, 1}, cb[6] = {0, 1, D == 3 ? 2 : 1, 1, 2, 2};
             C flux[NC], ringA[NC], ringB[NC], across[NC], cap1[NC], cap2[NC], capx[NC];
@@ -294,7 +294,7 @@ __global__ __launch_bounds__(TX *TY) void k_collide(
             });
             continue;
         } else {
-        gather_links<D, S, C, MASK>(A, g.qs, lm, nb, n, h, p.link_q);
+        gather_links<D, S, C, MASK, Ix>(A, g.qs, lm, nb, n, h, p.link_q);
         C drho, j[3];
         moments_of<D, C>(h, drho, j);
         C u[3] = {C(0), C(0), C(0)};
@@ -316,7 +316,7 @@ __global__ __launch_bounds__(TX *TY) void k_collide(
         }
         static_for<0, Lat<D>::Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
-            st_nt_at(B + i * g.qs, (unsigned)n, S(h[i]));
+            st_nt_at(B + i * g.qs, (Ix)n, S(h[i]));
         });
         }
     }
@@ -516,7 +516,8 @@ dim3 moment_grid(int D, const Geom &g) {
     return dim3((g.nx + TX - 1) / TX, (g.ny + TY - 1) / TY, D == 3 ? g.nz : 1);
 }
 
-template <int D, class S, class C, bool MASK> struct Launch {
+// Ix: index type of the population arrays (size_t: far_arrays)
+template <int D, class S, class C, bool MASK, class Ix> struct Launch {
     static dim3 collide_grid(const Geom &g) {
         return dim3((g.nx + TX - 1) / TX, (g.ny + TY - 1) / TY, D == 3 ? (g.nz + Tile<D>::ZB - 1) / Tile<D>::ZB : 1);
     }
@@ -543,17 +544,17 @@ template <int D, class S, class C, bool MASK> struct Launch {
     }
     static void moments(hipStream_t s, const void *A, const Geom &g, const uint32_t *links, const void *prm, void *rho,
                         void *gfl, double *orho, double *oU, double *partials) {
-        hipLaunchKernelGGL((k_moments<D, S, C, MASK>), moment_grid(D, g), dim3(256), 0, s, (const S *)A, g, links,
+        hipLaunchKernelGGL((k_moments<D, S, C, MASK, Ix>), moment_grid(D, g), dim3(256), 0, s, (const S *)A, g, links,
                            *(const Params<C> *)prm, (C *)rho, (C *)gfl, orho, oU, partials);
     }
     static void collide(hipStream_t s, const void *A, void *B, const Geom &g, const uint32_t *links, const void *prm,
                         const void *rho, const void *gfl) {
-        hipLaunchKernelGGL((k_collide<D, S, C, MASK, MODE_STEP>), collide_grid(g), dim3(256), 0, s, (const S *)A, (S *)B, g,
+        hipLaunchKernelGGL((k_collide<D, S, C, MASK, MODE_STEP, Ix>), collide_grid(g), dim3(256), 0, s, (const S *)A, (S *)B, g,
                            nullptr, links, *(const Params<C> *)prm, (const C *)rho, (const C *)gfl, nullptr);
     }
     static void pressure(hipStream_t s, const void *A, const Geom &g, const uint32_t *links, const void *prm,
                          const void *rho, double *out) {
-        hipLaunchKernelGGL((k_collide<D, S, C, MASK, MODE_PT>), collide_grid(g), dim3(256), 0, s, (const S *)A,
+        hipLaunchKernelGGL((k_collide<D, S, C, MASK, MODE_PT, Ix>), collide_grid(g), dim3(256), 0, s, (const S *)A,
                            (S *)nullptr, g, nullptr, links, *(const Params<C> *)prm, (const C *)rho, (const C *)nullptr,
                            out);
     }
@@ -594,13 +595,18 @@ int moment_block_count(int D, const Geom &g) {
     return (int)(gr.x * gr.y * gr.z);
 }
 
-KernelSet kernel_set(int D, bool fp64, bool masked) {
-    if (D == 2) {
-        if (fp64) return masked ? Launch<2, double, double, true>::set() : Launch<2, double, double, false>::set();
-        return masked ? Launch<2, float, float, true>::set() : Launch<2, float, float, false>::set();
-    }
-    if (fp64) return masked ? Launch<3, double, double, true>::set() : Launch<3, double, double, false>::set();
-    return masked ? Launch<3, float, float, true>::set() : Launch<3, float, float, false>::set();
+bool far_arrays(const Geom &g, bool fp64) { return (unsigned long long)g.N * (fp64 ? 8 : 4) > (1ull << 32); }
+
+namespace {
+template <int D, class Ix> KernelSet set_of(bool fp64, bool masked) {
+    if (fp64) return masked ? Launch<D, double, double, true, Ix>::set() : Launch<D, double, double, false, Ix>::set();
+    return masked ? Launch<D, float, float, true, Ix>::set() : Launch<D, float, float, false, Ix>::set();
+}
+}  // namespace
+
+KernelSet kernel_set(int D, bool fp64, bool masked, bool far) {
+    if (D == 2) return far ? set_of<2, size_t>(fp64, masked) : set_of<2, unsigned>(fp64, masked);
+    return far ? set_of<3, size_t>(fp64, masked) : set_of<3, unsigned>(fp64, masked);
 }
 
 long long reduce_scratch_rows(int n) {

@@ -190,3 +190,20 @@ def test_d2q9_kernels_are_found_by_their_exact_workgroup_shape():
                 for per in range(-1, 20):
                     got = find(fp64, masked, Shape(threads, per, 64, 8, 1))
                     assert bool(got) == ((threads, per) in shapes), (fp64, masked, threads, per)
+
+
+@pytest.mark.parametrize("nodes,fp64,far", [(2 ** 29, True, False), (2 ** 29 + 1, True, True), (2 ** 30, False, False),
+                                            (2 ** 30 + 1, False, True), (4096, True, False), (2 ** 31 - 64, True, True)])
+def test_population_arrays_past_32_bit_offsets_are_addressed_with_64(nodes, fp64, far):
+    # the byte offset of the last of `nodes` values fits 32 bits up to 4 GiB
+    import paper_2112_01975_amd as P
+
+    class Geom(ctypes.Structure):
+        _fields_ = [("nx", ctypes.c_int), ("ny", ctypes.c_int), ("nz", ctypes.c_int), ("px", ctypes.c_int),
+                    ("N", ctypes.c_int), ("qs", ctypes.c_longlong)]
+
+    f = ctypes.CDLL(P.lbm.LIB_PATH)._ZN3lbm10far_arraysERKNS_4GeomEb
+    f.restype = ctypes.c_bool
+    f.argtypes = [ctypes.POINTER(Geom), ctypes.c_bool]
+    assert f(Geom(nodes, 1, 1, nodes, nodes, nodes + 64), fp64) == far
+    assert (((nodes - 1) * (8 if fp64 else 4)) >> 32 != 0) == far
