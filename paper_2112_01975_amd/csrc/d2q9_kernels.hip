@@ -11,8 +11,8 @@
 //            update (eqs LBMeq, LBMstar, LBGK) in registers, post-collision populations back to
 //            LDS, or in the last step to the other lattice.
 // Nodes outside the tile are recomputed by the neighbouring workgroups. One loop body serves
-// every step of every tile, so the state does not depend on the tile or on how a run is cut
-// into launches, bit for bit.
+// every step of a tile, and the arithmetic rounds alike in every instance and in the other D2Q9
+// kernels, so the state does not depend on the tile or on how a run is cut into launches, bit for bit.
 #include <hip/hip_runtime.h>
 #include <math.h>
 

@@ -68,6 +68,10 @@ __device__ __forceinline__ double sqrt_c(double x) { return sqrt(x); }
 __device__ __forceinline__ float exp_c(float x) { return expf(x); }
 __device__ __forceinline__ double exp_c(double x) { return exp(x); }
 
+// a b + c in one rounding, written out where kernels must round alike
+__device__ __forceinline__ float fma_c(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_c(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 template <class C> struct Eos {
     int kind;
     C RT;   // R * T with T = T_reduced * Tc
@@ -95,10 +99,10 @@ template <class C> struct Eos {
         }
         case EOS_SC1: {   // P = rho/3 + (G/6) psi^2, psi = 1 - exp(-rho)
             const C s = one - exp_c(-r);
-            return r * C(1.0 / 3.0) + aa * C(1.0 / 6.0) * s * s;
+            return fma_c(r, C(1.0 / 3.0), aa * C(1.0 / 6.0) * s * s);
         }
         case EOS_SC2: {   // psi = exp(-1/rho): psi^2 = exp(-2/rho)
-            return r * C(1.0 / 3.0) + aa * C(1.0 / 6.0) * exp_c(C(-2) * rcp(r));
+            return fma_c(r, C(1.0 / 3.0), aa * C(1.0 / 6.0) * exp_c(C(-2) * rcp(r)));
         }
         default: return r * C(1.0 / 3.0);
         }
@@ -113,9 +117,11 @@ template <class C> struct Eos {
 };
 
 // signed pseudo-potential s*psi with psi = sqrt|P - P0|, P0 = rho/3, s = +1 iff P > P0
-// (eq force_form); neighbours use |s psi|, the centre its sign.
+// (eq force_form); neighbours use |s psi|, the centre its sign. The difference is one multiply-add
+// in every kernel: left to the compiler, a kernel that keeps rho/3 for the pressure as well
+// subtracts it rounded (FP32 psi then differs from the other kernels' in its last bits).
 template <class C> __device__ __forceinline__ C signed_psi(const Eos<C> &e, C r) {
-    C d = e.pressure(r) - r * C(1.0 / 3.0);
+    C d = fma_c(r, C(-1.0 / 3.0), e.pressure(r));
     C s = sqrt_c(fabs(d));
     return d > C(0) ? s : -s;
 }

@@ -232,10 +232,9 @@ __device__ __forceinline__ void collide(C (&h)[Lat<D>::Q], C rho, C drho, const 
     h[0] = rest;
 }
 
-// D2Q9 force and update with every multiply-add written out: compiled into several kernels, they
-// round alike in each, so that steps in tiles and the two-pass step agree bit for bit.
-__device__ __forceinline__ float fma_c(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double fma_c(double a, double b, double c) { return __builtin_fma(a, b, c); }
+// D2Q9 force and FP64 update with every multiply-add written out: compiled into several kernels, they
+// round alike in each. The rest of a step (moments, psi, the FP32 update of collide()) does too, so
+// that steps in tiles of any shape, with a thread per node and in two passes agree bit for bit.
 
 // Momentum source S = -F + rho g (eq Kforce_final) of one node. at(k, x, y) gives the density and
 // signed pseudo-potential at r + k (x, y); gw the ring factors of psi (axis, diagonal) and rho of the

@@ -81,6 +81,43 @@ def test_d2q9_tiles_of_several_steps(dims, walls, monkeypatch):
             assert max_rel(r, ref[0]) < tr and np.abs(U - ref[1]).max() < tu, (tile, prec)
 
 
+# every workgroup shape, one to four steps per launch
+_SHAPES = _TILES + ["256,1,12,8,1", "512,2,24,24,1", "512,3,12,12,4", "512,3,32,32,1", "1024,2,24,24,3"]
+
+
+@pytest.mark.parametrize("eos,tau_vapour", [(T.VDW, 0.0), (T.VDW, 1.1), (T.PR, 0.0), (T.RKS, 0.0), (T.CS, 0.0), (T.IDEAL, 0.0),
+                                            (T.SC1, 0.0), (T.SC2, 0.0)])
+@pytest.mark.parametrize("walls", [0, 1, 2])
+def test_d2q9_states_do_not_depend_on_the_tile(walls, eos, tau_vapour, monkeypatch):
+    # the same bits from every tile, from one thread per node and from the two-pass step
+    import paper_2112_01975_amd as P
+    nx, ny = 75, 41
+    fluid = {T.PR: dict(a=0.005046, acentric=0.344, T_reduced=0.6), T.RKS: dict(a=0.00915793, acentric=0.344, T_reduced=0.7),
+             T.CS: dict(a=0.0150367, T_reduced=0.7)}.get(eos, dict(a=0.02, T_reduced=0.8))
+    mask = L.random_mask(nx, ny, 1, 0.08, 31) if walls else None
+    case = Case(2, nx, ny, eos=eos, tau_vapour=tau_vapour, mask=mask, rho_wall=1.0, **fluid)
+    rv, rl = case.coexistence() if eos != T.IDEAL else (0.9, 1.1)
+    case.rho_wall = rv   # (walls between the phases diverge at the density ratio of 850 of the PR fluid)
+    rho0 = L.drop(nx, ny, 1, 10.0, rl, rv, 5.0, noise=1e-5, seed=32)
+    if mask is not None:
+        rho0 = np.where(mask.astype(bool), case.rho_wall, rho0)
+    for prec in (0, 1):
+        p = case.params(prec, rv if prec else 0.0, check_every=-1)
+        if eos != T.IDEAL:
+            p.rho_liquid, p.rho_vapour = rl, rv
+        if walls == 2:
+            p.link_q = np.random.default_rng(33).uniform(0.05, 0.95, (9, nx * ny))
+        monkeypatch.setenv("LBM2P_TWO_PASS", "1")
+        with P.Simulation(p) as s:
+            ref = P.lbm_get_populations(s.init(rho0).step(12).ctx)
+            assert np.all(np.isfinite(s.moments()[0])), "reference run diverged"
+        monkeypatch.setenv("LBM2P_TWO_PASS", "0")
+        for tile in _SHAPES:
+            monkeypatch.setenv("LBM2P_TILE", tile)
+            with P.Simulation(p) as s:
+                assert np.array_equal(P.lbm_get_populations(s.init(rho0).step(12).ctx), ref), (tile, prec)
+
+
 @pytest.mark.parametrize("walls", ["none", "halfway", "interpolated"])
 @pytest.mark.parametrize("prec", [0, 1])
 def test_d2q9_single_pass_matches_two_pass(walls, prec, monkeypatch):
