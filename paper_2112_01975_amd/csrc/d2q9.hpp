@@ -27,6 +27,7 @@ struct D2Tiles {
     int ntx, nty;      // tiles
     int nsteps;
     int first;         // 0: the step that pulls from the lattice
+    int stream;        // one thread per node: non-temporal stores (d2_stream)
     int chunk;         // consecutive tiles dealt to one XCD at a time
     unsigned inv_chunk, inv_ntx;   // 2^32 / d of these: division by a multiplication
     unsigned inv[kMaxTileSteps];   // 2^20 / width + 1 of the region's width by steps still to come
@@ -34,6 +35,9 @@ struct D2Tiles {
 };
 
 D2Tiles d2_tiles(const Geom &g, bool fp64, const D2Shape &sh, int nsteps);
+
+// Whether the kernel with a thread per node writes its lattice with non-temporal stores.
+bool d2_stream(const Geom &g, bool fp64);
 
 // whether a tile with its halo fits the workgroup's nodes and LDS
 bool d2_fits(bool fp64, const D2Shape &sh);

@@ -238,9 +238,9 @@ __global__ __launch_bounds__(NT) void k_d2q9(const S *__restrict__ A, S *__restr
 // the two-node halo. Only the tile's own nodes are collided and kept in registers, and two
 // workgroups share a CU, so this moves a large FP64 grid faster than the tiles above, whose
 // recomputed halo costs more there than the launches and traffic they save: 2040x1900 FP64 121 us
-// a step, 4.6 TB/s of populations against 5.4 for a copy, and 126 in tiles.
+// a step, 4.6 TB/s of populations against 5.4 for a copy, and 126 in tiles. NT: see d2_stream.
 constexpr int SX = 64, SY = 8, SHALO = 2;
-template <class S, class C, bool MASK, class Ix>
+template <class S, class C, bool MASK, class Ix, bool NT>
 __global__ __launch_bounds__(SX *SY) void k_d2q9_single(const S *__restrict__ A, S *__restrict__ B, Geom g,
                                                         const uint32_t *__restrict__ links, Params<C> p, D2Tiles tl) {
     constexpr int LX = SX + 2 * SHALO, LY = SY + 2 * SHALO, LS = LX * LY, NTH = SX * SY, NH = LS - NTH;
@@ -304,9 +304,11 @@ __global__ __launch_bounds__(SX *SY) void k_d2q9_single(const S *__restrict__ A,
     if (x >= g.nx || y >= g.ny || link_solid(olm)) return;
     const C gw[8] = {p.gw[0][0], p.gw[1][0], p.gw[0][2], p.gw[1][2], p.gw[0][1], p.gw[1][1], p.gw[0][3], p.gw[1][3]};
     update_node<C>(p, gw, s_rp + e, s_gx + e, s_gy + e, LX, p.rho_ref, p.accel[0], p.accel[1], drho, rinv, spsi, jj, h);
+    const Ix n = (Ix)(x + g.px * y);
     static_for<0, 9>([&](auto I) {
         constexpr int i = decltype(I)::value;
-        st_nt_at(B + i * g.qs, (Ix)(x + g.px * y), S(h[i]));
+        if constexpr (NT) st_nt_at(B + i * g.qs, n, S(h[i]));
+        else st_at(B + i * g.qs, n, S(h[i]));
     });
 }
 
@@ -327,8 +329,8 @@ void launch(hipStream_t s, const void *A, void *B, const Geom &g, const uint32_t
 template <class S, class C, bool MASK, class Ix>
 void launch_single(hipStream_t s, const void *A, void *B, const Geom &g, const uint32_t *links, const void *prm,
                    const D2Tiles &t) {
-    hipLaunchKernelGGL((k_d2q9_single<S, C, MASK, Ix>), dim3(blocks(t)), dim3(SX * SY), 0, s, (const S *)A, (S *)B, g, links,
-                       *(const Params<C> *)prm, t);
+    auto *kernel = t.stream ? k_d2q9_single<S, C, MASK, Ix, true> : k_d2q9_single<S, C, MASK, Ix, false>;
+    hipLaunchKernelGGL(kernel, dim3(blocks(t)), dim3(SX * SY), 0, s, (const S *)A, (S *)B, g, links, *(const Params<C> *)prm, t);
 }
 
 template <class S, class C, bool MASK>
@@ -352,6 +354,7 @@ D2Tiles d2_tiles(const Geom &g, bool fp64, const D2Shape &sh, int nsteps) {
     t.nty = (g.ny + t.ty - 1) / t.ty;
     t.nsteps = nsteps;
     t.first = 0;
+    t.stream = d2_stream(g, fp64);
     const int nt = t.ntx * t.nty, full = kXcds * kXcdChunk, rounds = (nt + full - 1) / full;
     t.chunk = (nt + kXcds * rounds - 1) / (kXcds * rounds);
     auto inverse = [](int d) { return (unsigned)std::min<unsigned long long>(((1ull << 32) + d - 1) / d, 0xFFFFFFFFull); };
@@ -363,6 +366,17 @@ D2Tiles d2_tiles(const Geom &g, bool fp64, const D2Shape &sh, int nsteps) {
             sizeof(int) * (size_t)(t.tx + t.ty + 4 * m0);
     for (int r = 0; r < kMaxTileSteps; ++r) t.inv[r] = (1u << 20) / (unsigned)(t.tx + 2 * (2 + 3 * r)) + 1u;
     return t;
+}
+
+// Non-temporal stores keep the lattice being read in the L2s while both fit there (32 MB), and
+// make no difference to a lattice that has to come from HBM again. Between the two the next
+// step finds an ordinarily stored lattice in the 256 MB memory-side cache. us per step,
+// non-temporal | ordinary, by the two lattices' size:
+//   FP32  22 MB 6.1 | 6.9    32 MB 10.3 | 8.5   141 MB 35.4 | 26.1   264 MB 61.2 | 55.6   302 MB 68.9 | 73.7
+//   FP64  32 MB 8.5 | 8.7    38 MB  9.9 | 9.4   151 MB 35.9 | 30.4   274 MB 60.6 | 60.1   560 MB 115 | 124
+bool d2_stream(const Geom &g, bool fp64) {
+    const double mb = 18e-6 * (fp64 ? 8 : 4) * (double)g.qs;
+    return mb < (fp64 ? 33.5 : 30.0) || mb > 268.0;
 }
 
 bool d2_fits(bool fp64, const D2Shape &sh) {

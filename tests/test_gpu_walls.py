@@ -118,6 +118,24 @@ def test_d2q9_states_do_not_depend_on_the_tile(walls, eos, tau_vapour, monkeypat
                 assert np.array_equal(P.lbm_get_populations(s.init(rho0).step(12).ctx), ref), (tile, prec)
 
 
+# lattices between the size of the L2s and that of the memory-side cache, where the kernel with a
+# thread per node stores them the ordinary way (44 and 47 MB; the other sizes here stay below)
+@pytest.mark.parametrize("prec,dims", [(0, (630, 480)), (1, (961, 660))])
+@pytest.mark.parametrize("walls", [False, True])
+def test_d2q9_ordinary_stores_agree_bit_for_bit(walls, prec, dims, monkeypatch):
+    import paper_2112_01975_amd as P
+    nx, ny = dims
+    mask = L.random_mask(nx, ny, 1, 0.05, 41) if walls else None
+    case = Case(2, nx, ny, a=0.02, T_reduced=0.8, rho_wall=2.0, mask=mask)
+    rho0, u0 = L.random_state(case.N, 2, 1.0, 1.3, 0.02, 42)
+    pops = []
+    for tile in ("512,0,64,8,1", "512,2,32,16,1"):
+        monkeypatch.setenv("LBM2P_TILE", tile)
+        with P.Simulation(case.params(prec, 1.0 if prec else 0.0)) as s:
+            pops.append(P.lbm_get_populations(s.init(rho0, u0).step(6).ctx))
+    assert np.array_equal(*pops)
+
+
 @pytest.mark.parametrize("walls", ["none", "halfway", "interpolated"])
 @pytest.mark.parametrize("prec", [0, 1])
 def test_d2q9_single_pass_matches_two_pass(walls, prec, monkeypatch):

@@ -207,3 +207,21 @@ def test_population_arrays_past_32_bit_offsets_are_addressed_with_64(nodes, fp64
     f.argtypes = [ctypes.POINTER(Geom), ctypes.c_bool]
     assert f(Geom(nodes, 1, 1, nodes, nodes, nodes + 64), fp64) == far
     assert (((nodes - 1) * (8 if fp64 else 4)) >> 32 != 0) == far
+
+
+@pytest.mark.parametrize("nx,ny,fp64,stream", [(64, 64, True, True), (448, 512, True, True), (512, 512, True, False),
+                                               (1344, 1376, True, False), (1408, 1376, True, True), (640, 640, False, True),
+                                               (672, 660, False, False), (1920, 1920, False, False), (2048, 2048, False, True)])
+def test_d2q9_lattices_between_the_caches_are_stored_the_ordinary_way(nx, ny, fp64, stream):
+    # two lattices of 9 populations past the L2s (FP64 33.5 MB, FP32 30 MB) and up to 268 MB
+    import paper_2112_01975_amd as P
+    f = ctypes.CDLL(P.lbm.LIB_PATH)._ZN3lbm9d2_streamERKNS_4GeomEb
+    f.restype = ctypes.c_bool
+
+    class Geom(ctypes.Structure):
+        _fields_ = [("nx", ctypes.c_int), ("ny", ctypes.c_int), ("nz", ctypes.c_int), ("px", ctypes.c_int),
+                    ("N", ctypes.c_int), ("qs", ctypes.c_longlong)]
+
+    f.argtypes = [ctypes.POINTER(Geom), ctypes.c_bool]
+    N = nx * ny
+    assert f(Geom(nx, ny, 1, nx, N, (N + 63) // 64 * 64 + 192), fp64) == stream
