@@ -48,6 +48,10 @@ using D2Launch = void (*)(hipStream_t, const void *A, void *B, const Geom &, con
 // kernel of a workgroup shape; nullptr when there is none
 D2Launch d2_launcher(bool fp64, bool masked, const D2Shape &sh);
 
+// the shape for launches of several steps (its `steps` at most), and for launches of one step
+D2Shape d2_plan(const Geom &g, bool fp64, bool masked, int cus);
+D2Shape d2_plan_one(const Geom &g, const D2Shape &plan);
+
 // the kernel with a thread per tile node for far_arrays, which the tiles do not address
 D2Launch d2_far_launcher(bool fp64, bool masked);
 

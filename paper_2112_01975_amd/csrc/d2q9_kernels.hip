@@ -397,4 +397,53 @@ D2Launch d2_launcher(bool fp64, bool masked, const D2Shape &sh) {
     return masked ? pick<float, float, true>(sh.threads, sh.per) : pick<float, float, false>(sh.threads, sh.per);
 }
 
+// The choice of the tiles: the least estimated time per step.
+// A launch costs about 4 us whatever it does (the gap to the next one, the prologue, the first
+// loads' latency). A workgroup then takes the vector instructions of its nodes, step by step with
+// their halo (0.133 us per 64 nodes and step in FP32, 0.25 in FP64), and its share of the memory
+// traffic (21 GB/s per CU); the two overlap in part. So small grids take several steps of tiny
+// tiles per launch, larger ones two steps of larger tiles. FP64 grids past 200,000 nodes are
+// bound by memory and by the halo's FP64 arithmetic: there one step per launch with a thread per
+// node is faster. Measured us per step: best tiles | one thread per node of 64 x 8 tiles:
+//   FP64  64^2 2.6 | 5.0   256^2 3.9 | 5.5   400x380 5.7 | 7.0   512^2 10.5 | 9.4   2040x1900 126 | 121
+//   FP32  64^2 2.2 | 4.0   256^2 3.0 | 4.2   512^2 5.1 | 5.7     1000x900 16.8 | 19     2048^2 63 | 68
+D2Shape d2_plan(const Geom &g, bool fp64, bool masked, int cus) {
+    static constexpr int shapes[][2] = {{256, 1}, {512, 2}, {512, 3}, {1024, 2}};
+    const int size = fp64 ? 8 : 4;
+    D2Shape best{SX * SY, 0, SX, SY, 1};
+    if (far_arrays(g, fp64) || (fp64 && (double)g.nx * g.ny > 200e3)) return best;
+    double least = -1.0;
+    for (const auto &wg : shapes)
+        for (int tx = 8; tx <= 64; tx += 8)
+            for (int ty = 4; ty <= 32; ty += 4)
+                for (int steps = 1; steps <= 3; ++steps) {
+                    const D2Shape sh{wg[0], wg[1], tx, ty, steps};
+                    if (!d2_fits(fp64, sh) || !d2_launcher(fp64, masked, sh)) continue;
+                    double waves = 0.0, first = 0.0;
+                    for (int r = 0; r < steps; ++r) {
+                        first = (double)(tx + 4 + 6 * r) * (ty + 4 + 6 * r);
+                        waves += ceil(first / 64.0);
+                    }
+                    const double rounds = ceil(ceil((double)g.nx / tx) * ceil((double)g.ny / ty) / cus);
+                    if (rounds > 3 && wg[0] == 1024) continue;   // one workgroup per CU: nothing overlaps its barriers
+                    const double compute = (fp64 ? 0.25 : 0.133) * waves;
+                    // rows of whole cache lines, unless every CU has a tile of its own (2048^2
+                    // FP32: 24 x 32 tiles 71 us a step, 32 x 24 ones 68)
+                    const double lines = rounds > 1 && tx * size % 128 ? 1.5 : 1.0;
+                    const double memory = lines * (first + tx * ty) * 9.0 * size / 21e3;
+                    const double overlap = fp64 && wg[1] == 3 ? 0.79 : 0.72;   // 139 KB of LDS
+                    const double us = (4.0 + overlap * rounds * (compute + memory)) / steps;
+                    if (least < 0.0 || us < least) { least = us; best = sh; }
+                }
+    return best;
+}
+
+// A launch of one step has the tiles' halo to recompute and nothing to save by it: from 64,000 nodes on a
+// thread per node is faster. us per step of one-step calls, tile of the plan | thread per node:
+//   FP32  256^2 4.8 | 4.8   300^2 5.8 | 5.1   640^2 10.2 | 7.6   1000x900 23.5 | 18.9   2048^2 94 | 70
+//   FP64  256^2 5.6 | 5.8   300^2 6.8 | 6.3   360^2 7.1 | 7.3    420^2 8.9 | 7.8
+D2Shape d2_plan_one(const Geom &g, const D2Shape &plan) {
+    return (double)g.nx * g.ny < 64e3 ? plan : D2Shape{SX * SY, 0, SX, SY, 1};
+}
+
 }  // namespace lbm

@@ -67,9 +67,9 @@ struct lbm_ctx {
     int graph_steps = 32;
     void *gA = nullptr;              // the lattice those captured steps start from
     bool use_graph = false;
-    D2Launch d2 = nullptr;           // D2Q9: steps in tiles instead of moments + collide
+    D2Launch d2[kMaxTileSteps] = {}; // D2Q9: launches of 1 .. tile_steps steps, instead of moments + collide
+    D2Tiles tiles[kMaxTileSteps];
     int tile_steps = 1;              // most steps per launch of those
-    D2Tiles tiles[kMaxTileSteps];    // launches of 1 .. tile_steps steps
     FusedLaunch fused = nullptr;     // single-pass step when available (D3Q27): the first segment's kernel
     std::vector<FusedSeg> segs;      // the launches of one fused step, over disjoint plane ranges
     bool initialized = false;
@@ -182,8 +182,8 @@ void fused_step(lbm_ctx *c) {
 
 // k steps from lattice a into b on stream s: one launch of the D2Q9 tiles, or the two-pass step (k = 1)
 void unfused_steps(lbm_ctx *c, hipStream_t s, const void *a, void *b, int k) {
-    if (c->d2) {
-        c->d2(s, a, b, c->g, c->links, params_ptr(c), c->tiles[k - 1]);
+    if (c->d2[0]) {
+        c->d2[k - 1](s, a, b, c->g, c->links, params_ptr(c), c->tiles[k - 1]);
     } else {
         c->ks.moments(s, a, c->g, c->links, params_ptr(c), c->rho, c->gfl, nullptr, nullptr, c->partials);
         c->ks.collide(s, a, b, c->g, c->links, params_ptr(c), c->rho, c->gfl);
@@ -322,55 +322,23 @@ int env_int(const char *name, int dflt) {
     return (v && *v) ? atoi(v) : dflt;
 }
 
-// Workgroup shape, tile and steps per launch of the D2Q9 step: the least estimated time per step.
-// A launch costs about 4 us whatever it does (the gap to the next one, the prologue, the first
-// loads' latency). A workgroup then takes the vector instructions of its nodes, step by step with
-// their halo (0.133 us per 64 nodes and step in FP32, 0.25 in FP64), and its share of the memory
-// traffic (21 GB/s per CU); the two overlap in part. So small grids take several steps of tiny
-// tiles per launch, larger ones two steps of larger tiles. FP64 grids past 200,000 nodes are
-// bound by memory and by the halo's FP64 arithmetic: there one step per launch with a thread per
-// node is faster. Measured us per step: this choice | one thread per node of 64 x 8 tiles:
-//   FP64  64^2 2.6 | 5.0   256^2 4.0 | 5.3   400x380 5.9 | 7.1   512^2 10.5 | 9.8   2040x1900 126 | 121
-//   FP32  64^2 2.2 | 4.0   256^2 3.0 | 4.2   512^2 5.1 | 5.7     1000x900 16.8 | 19     2048^2 63 | 68
+// D2Q9: the launches of 1 .. tile_steps steps.
 // LBM2P_TILE="threads,nodes per thread,width,height,steps" overrides ("512,0,64,8,1": one thread per node);
 // one that does not fit or has no kernel is ignored.
 void plan_tiles(lbm_ctx *c, int cus) {
-    static constexpr int shapes[][2] = {{256, 1}, {512, 2}, {512, 3}, {1024, 2}};
-    const int size = c->fp64 ? 8 : 4;
-    D2Shape best{512, 0, 64, 8, 1};
-    double least = -1.0;
+    D2Shape most = d2_plan(c->g, c->fp64, c->masked, cus), one = d2_plan_one(c->g, most);
     const bool far = far_arrays(c->g, c->fp64);
-    if (!far && !(c->fp64 && (double)c->g.nx * c->g.ny > 200e3))
-        for (const auto &wg : shapes)
-            for (int tx = 8; tx <= 64; tx += 8)
-                for (int ty = 4; ty <= 32; ty += 4)
-                    for (int steps = 1; steps <= 3; ++steps) {
-                        const D2Shape sh{wg[0], wg[1], tx, ty, steps};
-                        if (!d2_fits(c->fp64, sh) || !d2_launcher(c->fp64, c->masked, sh)) continue;
-                        double waves = 0.0, first = 0.0;
-                        for (int r = 0; r < steps; ++r) {
-                            first = (double)(tx + 4 + 6 * r) * (ty + 4 + 6 * r);
-                            waves += ceil(first / 64.0);
-                        }
-                        const double rounds = ceil(ceil((double)c->g.nx / tx) * ceil((double)c->g.ny / ty) / cus);
-                        if (rounds > 3 && wg[0] == 1024) continue;   // one workgroup per CU: nothing overlaps its barriers
-                        const double compute = (c->fp64 ? 0.25 : 0.133) * waves;
-                        // rows of whole cache lines, unless every CU has a tile of its own (2048^2
-                        // FP32: 24 x 32 tiles 71 us a step, 32 x 24 ones 68)
-                        const double lines = rounds > 1 && tx * size % 128 ? 1.5 : 1.0;
-                        const double memory = lines * (first + tx * ty) * 9.0 * size / 21e3;
-                        const double overlap = c->fp64 && wg[1] == 3 ? 0.79 : 0.72;   // 139 KB of LDS
-                        const double us = (4.0 + overlap * rounds * (compute + memory)) / steps;
-                        if (least < 0.0 || us < least) { least = us; best = sh; }
-                    }
     const char *e = getenv("LBM2P_TILE");
     D2Shape w{};
     if (!far && e && sscanf(e, "%d,%d,%d,%d,%d", &w.threads, &w.per, &w.tx, &w.ty, &w.steps) == 5 && d2_fits(c->fp64, w) &&
         d2_launcher(c->fp64, c->masked, w))
-        best = w;
-    c->tile_steps = best.steps;
-    for (int k = 1; k <= best.steps; ++k) c->tiles[k - 1] = d2_tiles(c->g, c->fp64, best, k);
-    c->d2 = far ? d2_far_launcher(c->fp64, c->masked) : d2_launcher(c->fp64, c->masked, best);
+        most = one = w;
+    c->tile_steps = most.steps;
+    for (int k = 1; k <= most.steps; ++k) {
+        const D2Shape &sh = k == 1 ? one : most;
+        c->tiles[k - 1] = d2_tiles(c->g, c->fp64, sh, k);
+        c->d2[k - 1] = far ? d2_far_launcher(c->fp64, c->masked) : d2_launcher(c->fp64, c->masked, sh);
+    }
 }
 
 }  // namespace
@@ -551,7 +519,7 @@ int lbm_create(const lbm_params *p, lbm_ctx **out) {
     const size_t pop = (size_t)c->Q * (size_t)c->g.qs * c->sbytes;
     if (hipMalloc(&c->A, pop) != hipSuccess || hipMalloc(&c->B, pop) != hipSuccess ||
         hipMalloc(&c->rho, N * cbytes) != hipSuccess ||
-        (!c->fused && !c->d2 && hipMalloc(&c->gfl, (size_t)c->D * N * cbytes) != hipSuccess) ||   // two-pass step only
+        (!c->fused && !c->d2[0] && hipMalloc(&c->gfl, (size_t)c->D * N * cbytes) != hipSuccess) ||   // two-pass step only
         hipMalloc((void **)&c->partials, (size_t)c->nblk * kPartialSlots * sizeof(double)) != hipSuccess ||
         hipMalloc((void **)&c->rscratch, (size_t)std::max(reduce_scratch_rows(c->nblk), reduce_scratch_rows(c->nfslots)) *
                                              kPartialSlots * sizeof(double)) != hipSuccess ||
@@ -695,13 +663,13 @@ int lbm_step_timed(lbm_ctx *c, int64_t n, double ms[3], int64_t launches[2]) {
     HIP_OR_FAIL(c, hipEventRecord(tot0, c->stream));
     for (int64_t t = 0; t < n; ++t) {
         HIP_OR_FAIL(c, hipEventRecord(ev[0], c->stream));
-        if (!c->fused && !c->d2)
+        if (!c->fused && !c->d2[0])
             c->ks.moments(c->stream, c->A, c->g, c->links, params_ptr(c), c->rho, c->gfl, nullptr, nullptr, c->partials);
         HIP_OR_FAIL(c, hipEventRecord(ev[1], c->stream));
         if (c->fused) {
             fused_step(c);
             c->folded = c->fold;
-        } else if (c->d2) {
+        } else if (c->d2[0]) {
             unfused_steps(c, c->stream, c->A, c->B, 1);
         } else {
             c->ks.collide(c->stream, c->A, c->B, c->g, c->links, params_ptr(c), c->rho, c->gfl);
@@ -726,7 +694,7 @@ int lbm_step_timed(lbm_ctx *c, int64_t n, double ms[3], int64_t launches[2]) {
     ms[0] = acc[0];
     ms[1] = acc[1];
     ms[2] = tt;
-    launches[0] = c->fused || c->d2 ? 0 : n;
+    launches[0] = c->fused || c->d2[0] ? 0 : n;
     launches[1] = n;
     return LBM_OK;
 }

@@ -118,6 +118,25 @@ def test_d2q9_states_do_not_depend_on_the_tile(walls, eos, tau_vapour, monkeypat
                 assert np.array_equal(P.lbm_get_populations(s.init(rho0).step(12).ctx), ref), (tile, prec)
 
 
+# from 64,000 nodes on, launches of one step take another kernel than those of several
+@pytest.mark.parametrize("walls", [False, True])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_d2q9_cut_of_a_run_changes_no_bit_on_larger_grids(prec, walls):
+    import paper_2112_01975_amd as P
+    nx, ny = 301, 230
+    mask = L.random_mask(nx, ny, 1, 0.05, 43) if walls else None
+    case = Case(2, nx, ny, a=0.02, T_reduced=0.8, rho_wall=2.0, mask=mask)
+    rho0, u0 = L.random_state(case.N, 2, 1.0, 1.3, 0.02, 44)
+    pops = []
+    for calls in ((70,), (1,) * 70, (35, 1, 2, 32)):
+        with P.Simulation(case.params(prec, 1.0 if prec else 0.0)) as s:
+            s.init(rho0, u0)
+            for n in calls:
+                s.step(n)
+            pops.append(P.lbm_get_populations(s.ctx))
+    assert np.array_equal(pops[0], pops[1]) and np.array_equal(pops[0], pops[2])
+
+
 # lattices between the size of the L2s and that of the memory-side cache, where the kernel with a
 # thread per node stores them the ordinary way (44 and 47 MB; the other sizes here stay below)
 @pytest.mark.parametrize("prec,dims", [(0, (630, 480)), (1, (961, 660))])

@@ -225,3 +225,37 @@ def test_d2q9_lattices_between_the_caches_are_stored_the_ordinary_way(nx, ny, fp
     f.argtypes = [ctypes.POINTER(Geom), ctypes.c_bool]
     N = nx * ny
     assert f(Geom(nx, ny, 1, nx, N, (N + 63) // 64 * 64 + 192), fp64) == stream
+
+
+class _Geom(ctypes.Structure):
+    _fields_ = [("nx", ctypes.c_int), ("ny", ctypes.c_int), ("nz", ctypes.c_int), ("px", ctypes.c_int),
+                ("N", ctypes.c_int), ("qs", ctypes.c_longlong)]
+
+
+class _Shape(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int) for n in ("threads", "per", "tx", "ty", "steps")]
+
+
+def _d2_plans(nx, ny, fp64, masked):
+    """(threads, nodes per thread, steps) of the launches of several steps and of one step, 256 CUs."""
+    import paper_2112_01975_amd as P
+    lib = ctypes.CDLL(P.lbm.LIB_PATH)
+    plan, one = lib._ZN3lbm7d2_planERKNS_4GeomEbbi, lib._ZN3lbm11d2_plan_oneERKNS_4GeomERKNS_7D2ShapeE
+    plan.restype = one.restype = _Shape
+    plan.argtypes = [ctypes.POINTER(_Geom), ctypes.c_bool, ctypes.c_bool, ctypes.c_int]
+    one.argtypes = [ctypes.POINTER(_Geom), ctypes.POINTER(_Shape)]
+    px = (nx + 31) // 32 * 32 if nx >= 64 else nx
+    g = _Geom(nx, ny, 1, px, px * ny, (px * ny + 63) // 64 * 64 + 192)
+    p = plan(g, fp64, masked, 256)
+    return [(s.threads, s.per, s.steps) for s in (p, one(g, p))]
+
+
+@pytest.mark.parametrize("fp64", [False, True])
+def test_d2q9_one_step_launches_of_large_grids_take_a_thread_per_node(fp64):
+    # tiles of several steps, launched for one, took up to 1.36 times as long (2048^2 FP32)
+    for nx, ny in ((256, 256), (300, 300), (1000, 900), (2048, 2048), (5000, 65)):
+        several, one = _d2_plans(nx, ny, fp64, False)
+        assert one == (512, 0, 1)
+    for nx, ny in ((64, 64), (200, 300), (1, 9), (16, 2000)):
+        several, one = _d2_plans(nx, ny, fp64, False)
+        assert several[2] > 1 and one == several
