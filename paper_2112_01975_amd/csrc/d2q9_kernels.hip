@@ -402,16 +402,23 @@ D2Launch d2_launcher(bool fp64, bool masked, const D2Shape &sh) {
 // loads' latency). A workgroup then takes the vector instructions of its nodes, step by step with
 // their halo (0.133 us per 64 nodes and step in FP32, 0.25 in FP64), and its share of the memory
 // traffic (21 GB/s per CU); the two overlap in part. So small grids take several steps of tiny
-// tiles per launch, larger ones two steps of larger tiles. FP64 grids past 200,000 nodes are
-// bound by memory and by the halo's FP64 arithmetic: there one step per launch with a thread per
-// node is faster. Measured us per step: best tiles | one thread per node of 64 x 8 tiles:
-//   FP64  64^2 2.6 | 5.0   256^2 3.9 | 5.5   400x380 5.7 | 7.0   512^2 10.5 | 9.4   2040x1900 126 | 121
-//   FP32  64^2 2.2 | 4.0   256^2 3.0 | 4.2   512^2 5.1 | 5.7     1000x900 16.8 | 19     2048^2 63 | 68
+// tiles per launch, larger ones two steps of larger tiles.
+// One step per launch with a thread per node is faster, and taken, on FP64 grids past 190,000 nodes
+// (bound by memory and by the halo's FP64 arithmetic), and on FP32 grids from 275,000 nodes (the
+// tiles' second round on the CUs) to lattices of 268 MB (d2_stream), but for flat or narrow ones,
+// whose rows of tiles are spread over several XCDs or whose lanes are idle. Measured us per
+// step: best tiles | one thread per node of 64 x 8 tiles:
+//   FP64  64^2 2.6 | 5.0    256^2 3.9 | 5.5     400x380 5.7 | 7.0   448x440 9.3 | 8.1   2040x1900 126 | 115
+//   FP32  64^2 2.2 | 4.0    256^2 3.0 | 4.2     512^2 5.1 | 5.7     353x852 7.1 | 6.1   641x482 7.3 | 6.2
+//         640^2 8.3 | 8.0   922x488 10.1 | 8.5  800^2 13.1 | 11.7   1500x1300 31 | 26   2048^2 60 | 69
+//         20000x16 6.6 | 8.4
 D2Shape d2_plan(const Geom &g, bool fp64, bool masked, int cus) {
     static constexpr int shapes[][2] = {{256, 1}, {512, 2}, {512, 3}, {1024, 2}};
     const int size = fp64 ? 8 : 4;
     D2Shape best{SX * SY, 0, SX, SY, 1};
-    if (far_arrays(g, fp64) || (fp64 && (double)g.nx * g.ny > 200e3)) return best;
+    const double nodes = (double)g.nx * g.ny;
+    const bool square = g.ny >= 32 * SY && (g.nx + SX - 1) / SX * SX <= 1.2 * g.nx;
+    if (far_arrays(g, fp64) || (fp64 ? nodes > 190e3 : nodes > 275e3 && 72e-6 * (double)g.qs < 268.0 && square)) return best;
     double least = -1.0;
     for (const auto &wg : shapes)
         for (int tx = 8; tx <= 64; tx += 8)

@@ -259,3 +259,14 @@ def test_d2q9_one_step_launches_of_large_grids_take_a_thread_per_node(fp64):
     for nx, ny in ((64, 64), (200, 300), (1, 9), (16, 2000)):
         several, one = _d2_plans(nx, ny, fp64, False)
         assert several[2] > 1 and one == several
+
+
+@pytest.mark.parametrize("nx,ny,fp64,steps_of_one", [
+    (448, 440, True, True), (420, 420, True, False), (2040, 1900, True, True),                    # FP64: past 190,000 nodes
+    (512, 512, False, False), (600, 500, False, True), (353, 852, False, True), (640, 640, False, True),   # FP32: past 275,000
+    (1900, 1900, False, True), (2048, 2048, False, False),                                        # and up to 268 MB
+    (20000, 16, False, False), (65, 5000, False, False)])                                         # but flat or narrow
+def test_d2q9_grids_on_which_tiles_of_several_steps_lost_take_a_thread_per_node(nx, ny, fp64, steps_of_one):
+    for masked in (False, True):
+        several, _ = _d2_plans(nx, ny, fp64, masked)
+        assert (several == (512, 0, 1)) == steps_of_one
