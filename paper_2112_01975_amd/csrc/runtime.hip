@@ -410,15 +410,20 @@ int lbm_create(const lbm_params *p, lbm_ctx **out) {
     // Small grids: a work item marches its planes one after another, so a grid too small to give
     // every CU an item of some planes is faster in the two-pass step, parallel over all nodes.
     // One plane of the single pass takes about 4.9 us in FP32 and 10.1 in FP64, the two passes
-    // 0.094 and 0.22 us per 1000 nodes; near the line, single pass | two passes, us per step:
-    // 64^3 FP32 90 | 25, FP64 178 | 52; 96^3 FP32 77 | 84, FP64 161 | 200 (10-plane chunks). With
+    // 0.094 and 0.22 us per 1000 nodes, or 0.03 and 0.06 plus 0.05 and 0.13 per 1000 lanes of their
+    // 64 x 4 x 2 tiles where many are idle; near the line, single pass | two passes, us per step:
+    // 64^3 FP32 37 | 25, FP64 57 | 50; 96^3 FP32 70 | 82, FP64 153 | 195; 16x16x4096 FP32 95 | 210,
+    // FP64 333 | 580; 8x300x300 FP32 131 | 292, FP64 483 | 813; 33x129x257 FP64 236 | 334. With
     // walls, whose planes cost more, the line is 16-plane chunks for every CU. LBM2P_FUSED=1
     // takes the single-pass step at any size.
     const bool plain_box = c->D == 3 && !c->masked;
     const int nzg = c->g.nz;
     long long nz64 = 1, nz32 = 1;
     const long long tiles64 = tile_count(64, 8), cost64 = split(tiles64, nzg, 4, &nz64);
-    const double single_us = (c->fp64 ? 10.1 : 4.9) * (double)cost64, two_us = (c->fp64 ? 0.22e-3 : 0.094e-3) * (double)c->g.N;
+    const double lanes = 64.0 * ((c->g.nx + 63) / 64) * 4.0 * ((c->g.ny + 3) / 4) * 2.0 * ((nzg + 1) / 2), nodes = (double)c->g.N;
+    const double single_us = (c->fp64 ? 10.1 : 4.9) * (double)cost64;
+    const double two_us = c->fp64 ? std::max(0.22e-3 * nodes, 0.06e-3 * nodes + 0.13e-3 * lanes)
+                                  : std::max(0.094e-3 * nodes, 0.03e-3 * nodes + 0.05e-3 * lanes);
     const bool few_items = plain_box ? single_us > two_us : tiles64 * std::max(1, nzg / 16) < cus;
     // FP32 boxes without walls also have 32 x 16 tiles: 15% slower per plane (more misaligned
     // lines, less halo), but some widths waste fewer lanes and items with them

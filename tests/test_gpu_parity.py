@@ -907,3 +907,26 @@ def test_small_grids_take_the_two_pass_step_by_default(monkeypatch):
                 r_g, U_g, _ = s.moments()
                 r_o, U_o, _ = run_oracle(case, rho0, None, 20)
                 assert max_rel(r_g, r_o) <= FP64_RHO_TOL and np.abs(U_g - U_o).max() <= FP64_U_TOL
+
+
+# the step a box without walls takes by itself (FP64, FP32): cubes around the line, boxes whose rows
+# leave most lanes of the two passes' tiles idle, flat ones; and its state against the two-pass step
+@pytest.mark.parametrize("dims,single_pass", [((64, 64, 64), (False, False)), ((80, 80, 80), (True, False)), ((96, 96, 96), (True, True)),
+                                              ((150, 141, 130), (True, True)), ((8, 300, 300), (True, True)), ((16, 16, 4096), (True, True)),
+                                              ((33, 129, 257), (True, True)), ((512, 512, 1), (False, False))])
+def test_default_step_of_plain_boxes(dims, single_pass, monkeypatch):
+    import paper_2112_01975_amd as P
+    monkeypatch.delenv("LBM2P_FUSED", raising=False)
+    case = Case(3, *dims, a=0.02, T_reduced=0.8)
+    rho0, u0 = L.random_state(case.N, 3, 1.0, 1.3, 0.02, 51)
+    for prec in (0, 1):
+        got = []
+        for two_pass in ("0", "1"):
+            monkeypatch.setenv("LBM2P_TWO_PASS", two_pass)
+            with P.Simulation(case.params(prec, 1.0 if prec else 0.0)) as s:
+                s.init(rho0, u0)
+                _, nl = P.lbm_step_timed(s.ctx, 3)
+                assert (nl[0] == 0) == (single_pass[prec] and two_pass == "0"), (dims, prec, list(nl))
+                got.append(s.moments())
+        tol, utol = (1e-12, 1e-12) if prec == 0 else (1e-5, 1e-6)   # bounds of the two-pass comparisons above
+        assert max_rel(got[0][0], got[1][0]) < tol and np.abs(got[0][1] - got[1][1]).max() < utol
