@@ -16,8 +16,13 @@ namespace lbm {
 namespace {
 
 constexpr int kWorkers = 8;
-constexpr size_t kChunk = size_t(2) << 20;   // pinning memory takes a new context's first copy about 0.2 ms per MiB
-constexpr size_t kLeast = size_t(4) << 20;   // smaller copies are not worth the threads
+constexpr size_t kChunk = size_t(2) << 20;
+// Copies of up to this many bytes go directly: the workers' threads, and for a process's first
+// large copy the pinning, would take longer. ms, direct | workers | workers, pinning included:
+//   to the device    5 MB 0.15 | 0.21 | 0.30   16 MB 0.44 | 0.53 | 0.69   32 MB 0.87 | 0.99 | 1.21   48 MB 1.64 | 1.40 | 1.60
+//   to the host      5 MB 0.27 | 0.20 | 0.30    6 MB 0.33 | 0.24 | 0.29   16 MB 0.90 | 0.54 | 0.65   48 MB 2.77 | 1.33 | 1.50
+// (to a fresh array of 48 MB 4.69 | 1.42 | 1.51; chunks of 1 MiB 48 MB 1.62, 512 KiB 2.30)
+constexpr size_t least(hipMemcpyKind kind) { return kind == hipMemcpyHostToDevice ? size_t(38) << 20 : size_t(6) << 20; }
 
 std::mutex g_mu;            // holders and the buffer
 int g_holders = 0;
@@ -102,10 +107,10 @@ void staging_release() {
 }
 
 hipError_t copy_pageable(int dev, hipStream_t stream, void *dst, const void *src, size_t bytes, hipMemcpyKind kind) {
-    const int n = (int)std::min<size_t>((size_t)worker_count(), (bytes + kChunk - 1) / kChunk);
     const void *host = kind == hipMemcpyHostToDevice ? src : dst;
+    const int n = bytes <= least(kind) ? 1 : worker_count();
     // (hipStreamPerThread names another stream in each worker, not ordered with the caller's)
-    if (bytes <= kLeast || n < 2 || stream == hipStreamPerThread || capturing(stream) || !pageable(host) || !take())
+    if (n < 2 || stream == hipStreamPerThread || capturing(stream) || !pageable(host) || !take())
         return hipMemcpyAsync(dst, src, bytes, kind, stream);
     std::atomic<size_t> next{0};
     std::atomic<int> err{(int)hipSuccess};

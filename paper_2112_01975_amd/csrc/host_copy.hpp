@@ -7,12 +7,13 @@
 namespace lbm {
 
 // Copies `bytes` between pageable host memory and device `dev` on `stream`, one of that device.
-// The caller's current device stays as it is. Copies of more than 4 MiB are complete on return; smaller ones, those of memory that
-// is not pageable, those on hipStreamPerThread and those into a capture go to hipMemcpyAsync. The
-// runtime's own copy of pageable memory goes through one thread at about 10 GB/s; here worker threads take turns on the stream, each with a pinned 2 MiB of its
-// own, so that one's transfer overlaps the others' copies (and the page faults of a fresh
-// array). 160 x 144 x 128 FP64, density and velocity in and density, velocity and pressure tensor
-// out (330 MB): 27 ms by the runtime's copies, 10 ms so.
+// The caller's current device stays as it is. Copies of more than 38 MiB to the device and 6 MiB to
+// the host are complete on return; smaller ones, those of memory that is not pageable, those on
+// hipStreamPerThread and those into a capture go to hipMemcpyAsync. The runtime's own copy of
+// pageable memory goes through one thread, 18 GB/s to the host (10 into fresh arrays) and 29 to the
+// device past 40 MB; here worker threads take turns on the stream, each with a pinned 2 MiB of its
+// own, so that one's transfer overlaps the others' copies (and the page faults of a fresh array):
+// 35 GB/s either way.
 hipError_t copy_pageable(int dev, hipStream_t stream, void *dst, const void *src, size_t bytes, hipMemcpyKind kind);
 
 // The pinned buffer is shared by all contexts of a process, 16 MiB; it is freed when the last

@@ -137,6 +137,20 @@ int main(int argc, char **argv) {
     staging_hold();
     if (check == "data") {
         (void)round_trip((hipStream_t) nullptr);
+    } else if (check == "worth_the_threads") {
+        // one direct copy up to the sizes from which the workers are faster, several beyond
+        std::vector<char> a(size_t(41) << 20), b(a.size());
+        const struct { size_t mib; hipMemcpyKind kind; bool direct; } cases[] = {
+            {1, hipMemcpyHostToDevice, true}, {5, hipMemcpyHostToDevice, true}, {38, hipMemcpyHostToDevice, true},
+            {41, hipMemcpyHostToDevice, false}, {1, hipMemcpyDeviceToHost, true}, {6, hipMemcpyDeviceToHost, true},
+            {7, hipMemcpyDeviceToHost, false}};
+        for (const auto &c : cases) {
+            copies.clear();
+            EXPECT(copy_pageable(0, (hipStream_t) nullptr, b.data(), a.data(), c.mib << 20, c.kind) == hipSuccess);
+            int n = 0;
+            for (const auto &t : copies) n += t.second;
+            EXPECT((n == 1) == c.direct);
+        }
     } else if (check == "per_thread_stream") {
         // that handle names another stream in every thread: only the caller's is the one meant
         EXPECT(round_trip(hipStreamPerThread) == 1);

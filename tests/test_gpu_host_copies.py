@@ -151,3 +151,23 @@ def test_batch_moments_into_device_and_pinned_arrays():
                 assert np.array_equal(got[:c.N], rho) and np.array_equal(got[c.N:], U.ravel()) and np.array_equal(t, tot)
     finally:
         P.lbm_batch_destroy(b)
+
+
+# fields and populations of more than 38 MiB each, which go up through the workers too; padded rows
+@pytest.mark.parametrize("dims,prec", [((192, 176, 170), 0), ((250, 240, 190), 1)])
+def test_large_uploads(dims, prec):
+    import paper_2112_01975_amd as P
+    case = Case(3, *dims, a=0.02, T_reduced=0.8)
+    rv, rl = case.coexistence()
+    rng = np.random.default_rng(61)
+    rho0, u0 = rng.uniform(rv, rl, case.N), rng.uniform(-0.01, 0.01, (3, case.N))
+    with P.Simulation(case.params(prec, rv if prec else 0.0)) as s:
+        s.init(rho0, u0)
+        rho, U, _ = s.moments()
+        assert np.abs(rho / rho0 - 1.0).max() <= (1e-13 if prec == 0 else 2e-6)   # 27 terms of 2**-52 or 2**-24
+        pops = P.lbm_get_populations(s.ctx)
+        s.step(1)
+        P.lbm_set_populations(s.ctx, pops)
+        assert np.array_equal(P.lbm_get_populations(s.ctx), pops)
+        r2, U2, _ = s.moments()
+        assert np.array_equal(r2, rho) and np.array_equal(U2, U)
