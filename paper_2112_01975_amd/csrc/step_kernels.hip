@@ -363,12 +363,12 @@ __global__ __launch_bounds__(TX *TY) void k_velocity3(Geom g, const uint32_t *__
             s_psi[slot + e] = signed_psi(p.eos, r[m]);
         }
     };
-    C r[PER];
-#pragma unroll 1
-    for (int j = -2; j <= 2; ++j) {
-        load(j, r);
-        stage(j, r);
-    }
+    // the first five planes' loads together, one latency instead of five
+    C first[5][PER], r[PER];
+#pragma unroll
+    for (int j = 0; j < 5; ++j) load(j - 2, first[j]);
+#pragma unroll
+    for (int j = 0; j < 5; ++j) stage(j - 2, first[j]);
     __syncthreads();
     const int e0 = (ty + HALO) * LX + tx + HALO;
     const long long Nu = (long long)g.nx * g.ny * g.nz;
@@ -562,9 +562,12 @@ template <int D, class S, class C, bool MASK, class Ix> struct Launch {
                          double *oU) {
         if constexpr (D == 3) {
             // planes per workgroup: long marches (each re-stages four planes), but about four
-            // workgroups per CU while chunks of four planes or more give them
-            const long long cols = (long long)((g.nx + TX - 1) / TX) * ((g.ny + TY - 1) / TY);
-            const int tz = (int)std::min<long long>(32, std::max<long long>(4, cols * g.nz / 1024));
+            // workgroups per CU while chunks of four planes or more give them; small grids take
+            // shorter ones as long as they get by with two per CU (fields in us, chunks of four
+            // planes | these: 32^3 FP64 17.6 | 12.5, 64^3 FP32 20.3 | 16.1, FP64 26.2 | 23.1; two
+            // planes at 128x128x32 FP64 47.4, four 43.9)
+            const long long cols = (long long)((g.nx + TX - 1) / TX) * ((g.ny + TY - 1) / TY), planes = cols * g.nz;
+            const int tz = (int)std::min<long long>(32, std::max<long long>(std::min<long long>(4, (planes + 511) / 512), planes / 1024));
             hipLaunchKernelGGL((k_velocity3<C, MASK>),
                                dim3((g.nx + TX - 1) / TX, (g.ny + TY - 1) / TY, (g.nz + tz - 1) / tz), dim3(TX * TY), 0, s, g,
                                links, *(const Params<C> *)prm, (const C *)rho, oU, tz);

@@ -930,3 +930,16 @@ def test_default_step_of_plain_boxes(dims, single_pass, monkeypatch):
                 got.append(s.moments())
         tol, utol = (1e-12, 1e-12) if prec == 0 else (1e-5, 1e-6)   # bounds of the two-pass comparisons above
         assert max_rel(got[0][0], got[1][0]) < tol and np.abs(got[0][1] - got[1][1]).max() < utol
+
+
+# chunks of one, two and three planes of the velocity pass, the last chunk ragged
+@pytest.mark.parametrize("masked", [False, True])
+@pytest.mark.parametrize("dims", [(70, 30, 7), (130, 61, 15), (130, 61, 25)])
+def test_output_fields_in_short_marches_match_the_oracle(dims, masked):
+    N = dims[0] * dims[1] * dims[2]
+    mask = L.random_mask(*dims, 0.1, 12) if masked else None
+    case = Case(3, *dims, a=0.02, T_reduced=0.8, rho_wall=2.0, mask=mask)
+    rho0, u0 = L.random_state(N, 3, 1.0, 1.3, 0.02, 6)
+    r_o, U_o, _ = run_oracle(case, rho0, u0, 1)
+    r_g, U_g, _ = run_gpu(case, rho0, u0, 1)
+    assert max_rel(r_g, r_o) < 1e-10 and np.abs(U_g - U_o).max() < 1e-10   # the parity bound
