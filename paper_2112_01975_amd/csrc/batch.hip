@@ -55,7 +55,8 @@ struct CaseDesc {
 // pull gather, the field arrays, 1- and 2-ring neighbour indices and the store. GlobalView
 // addresses the case's device arrays; TileView a tile of a D2Q9 case held in LDS. Both
 // designs run the same arithmetic in the same order, so they give the same bits.
-template <int D, class S, class C> struct GlobalView {
+// (Ix: index type of the populations; size_t for arrays past 4 GiB)
+template <int D, class S, class C, class Ix> struct GlobalView {
     const Geom &g;
     const uint8_t *mask;
     const S *A;
@@ -71,17 +72,9 @@ template <int D, class S, class C> struct GlobalView {
     }
     __device__ __forceinline__ bool solid(int n) const { return mask && mask[n]; }
     __device__ __forceinline__ int global_index(int n) const { return n; }
-    // arrays past 4 GiB (far_arrays): of the cases a batch accepts only FP64 D2Q9 can have them
-    __device__ __forceinline__ bool far() const {
-        return D == 2 && sizeof(S) == 8 && (unsigned long long)g.N * sizeof(S) > (1ull << 32);
-    }
-    template <class Ix> __device__ __forceinline__ void gather_as(const Node &nd, int n, C (&h)[Lat<D>::Q]) const {
+    __device__ __forceinline__ void gather_at(const Node &nd, int n, C (&h)[Lat<D>::Q]) const {
         if (mask) gather<D, S, C, true, Ix>(A, g.qs, mask, nd.nb, n, h);
         else gather<D, S, C, false, Ix>(A, g.qs, mask, nd.nb, n, h);
-    }
-    __device__ __forceinline__ void gather_at(const Node &nd, int n, C (&h)[Lat<D>::Q]) const {
-        if (far()) gather_as<size_t>(nd, n, h);
-        else gather_as<unsigned>(nd, n, h);
     }
     __device__ __forceinline__ int at1(const Node &nd, int cx, int cy, int cz) const { return nd.nb.at(cx, cy, cz); }
     __device__ __forceinline__ int at2(const Node &nd, int cx, int cy, int cz) const {
@@ -92,10 +85,7 @@ template <int D, class S, class C> struct GlobalView {
     __device__ __forceinline__ C &rho(int n) const { return frho[n]; }
     __device__ __forceinline__ C &psi(int n) const { return fpsi[n]; }
     __device__ __forceinline__ C &gfield(int a, int n) const { return fg[a * g.N + n]; }
-    __device__ __forceinline__ void store(int i, int n, C v) const {
-        if (far()) st_at(B + i * g.qs, (size_t)n, S(v));
-        else st_at(B + i * g.qs, (unsigned)n, S(v));
-    }
+    __device__ __forceinline__ void store(int i, int n, C v) const { st_at(B + i * g.qs, (Ix)n, S(v)); }
 };
 
 // phase 1 at node n (view coordinates nd): rho, signed psi and g = rho u^3 of the current
@@ -173,20 +163,20 @@ __device__ __forceinline__ void phase2_at(const V &v, const Params<C> &p, int n,
     });
 }
 
-template <int D, class S, class C>
-__device__ __forceinline__ GlobalView<D, S, C> global_view(const CaseDesc &cd, const S *A, S *B) {
-    return GlobalView<D, S, C>{cd.g, cd.mask, A, B, (C *)cd.frho, (C *)cd.fpsi, (C *)cd.fg};
+template <int D, class S, class C, class Ix>
+__device__ __forceinline__ GlobalView<D, S, C, Ix> global_view(const CaseDesc &cd, const S *A, S *B) {
+    return GlobalView<D, S, C, Ix>{cd.g, cd.mask, A, B, (C *)cd.frho, (C *)cd.fpsi, (C *)cd.fg};
 }
 
-template <int D, class S, class C>
+template <int D, class S, class C, class Ix>
 __device__ __forceinline__ void phase1_node(const CaseDesc &cd, const Params<C> &p, const S *A, int n) {
-    const auto v = global_view<D, S, C>(cd, A, nullptr);
+    const auto v = global_view<D, S, C, Ix>(cd, A, nullptr);
     phase1_at<D, S, C>(v, p, n, v.node(n));
 }
 
-template <int D, class S, class C>
+template <int D, class S, class C, class Ix>
 __device__ __forceinline__ void phase2_node(const CaseDesc &cd, const Params<C> &p, const S *A, S *B, int n) {
-    const auto v = global_view<D, S, C>(cd, A, B);
+    const auto v = global_view<D, S, C, Ix>(cd, A, B);
     if (!v.solid(n)) phase2_at<D, S, C>(v, p, n, v.node(n));
 }
 
@@ -343,16 +333,16 @@ __global__ __launch_bounds__(4 * CL) void k_batch_tile(const CaseDesc *__restric
 }
 
 // the whole step loop of one case in one workgroup (persistent design)
-template <int D, class S, class C>
+template <int D, class S, class C, class Ix>
 __device__ void case_steps(const CaseDesc &cd, const Params<C> &p, int nsteps, int parity) {
     S *L0 = (S *)cd.A, *L1 = (S *)cd.B;
     for (int st = 0; st < nsteps; ++st) {
         const bool even = ((st + parity) & 1) == 0;
         const S *A = even ? L0 : L1;
         S *B = even ? L1 : L0;
-        for (int n = threadIdx.x; n < cd.g.N; n += blockDim.x) phase1_node<D, S, C>(cd, p, A, n);
+        for (int n = threadIdx.x; n < cd.g.N; n += blockDim.x) phase1_node<D, S, C, Ix>(cd, p, A, n);
         __syncthreads();
-        for (int n = threadIdx.x; n < cd.g.N; n += blockDim.x) phase2_node<D, S, C>(cd, p, A, B, n);
+        for (int n = threadIdx.x; n < cd.g.N; n += blockDim.x) phase2_node<D, S, C, Ix>(cd, p, A, B, n);
         __syncthreads();
     }
 }
@@ -368,7 +358,7 @@ struct Work {
 };
 constexpr int kStepMaxBlock = 256;   // largest threads per block of the stepped kernels
 
-template <int D, int PHASE, int NPT>
+template <int D, int PHASE, int NPT, class Ix = unsigned>
 __global__ __launch_bounds__(kStepMaxBlock) void k_batch_phase(const CaseDesc *__restrict__ cases,
                                                                const Work *__restrict__ work, int st,
                                                                const int *__restrict__ parity) {
@@ -385,8 +375,8 @@ __global__ __launch_bounds__(kStepMaxBlock) void k_batch_phase(const CaseDesc *_
         for (int m = 0; m < NPT; ++m) {
             const int n = n0 + m * stride;
             if (n >= cd.g.N) break;
-            if constexpr (PHASE == 1) phase1_node<D, double, double>(cd, cd.pd, A, n);
-            else phase2_node<D, double, double>(cd, cd.pd, A, B, n);
+            if constexpr (PHASE == 1) phase1_node<D, double, double, Ix>(cd, cd.pd, A, n);
+            else phase2_node<D, double, double, Ix>(cd, cd.pd, A, B, n);
         }
     } else {
         const float *A = (const float *)(even ? cd.A : cd.B);
@@ -395,8 +385,8 @@ __global__ __launch_bounds__(kStepMaxBlock) void k_batch_phase(const CaseDesc *_
         for (int m = 0; m < NPT; ++m) {
             const int n = n0 + m * stride;
             if (n >= cd.g.N) break;
-            if constexpr (PHASE == 1) phase1_node<D, float, float>(cd, cd.pf, A, n);
-            else phase2_node<D, float, float>(cd, cd.pf, A, B, n);
+            if constexpr (PHASE == 1) phase1_node<D, float, float, Ix>(cd, cd.pf, A, n);
+            else phase2_node<D, float, float, Ix>(cd, cd.pf, A, B, n);
         }
     }
 }
@@ -409,15 +399,15 @@ constexpr Split kSplits[] = {{256, 1}, {128, 1}, {64, 1}, {256, 2}, {128, 2}, {6
 
 // one kernel per lattice: the register budget of a D2Q9 sweep is not set by the D3Q27 body
 // (D3Q27 cases run with at most 256 threads, which leaves room for the 27-population body)
-template <int D>
+template <int D, class Ix = unsigned>
 __global__ __launch_bounds__(D == 2 ? 1024 : 256) void k_batch(const CaseDesc *__restrict__ cases, const int *__restrict__ order,
                                                  int ncases, int nsteps, const int *__restrict__ parity) {
     const int c = order[blockIdx.x];
     if (c >= ncases) return;
     const CaseDesc cd = cases[c];
     const int par = parity[c];
-    if (cd.fp64) case_steps<D, double, double>(cd, cd.pd, nsteps, par);
-    else case_steps<D, float, float>(cd, cd.pf, nsteps, par);
+    if (cd.fp64) case_steps<D, double, double, Ix>(cd, cd.pd, nsteps, par);
+    else case_steps<D, float, float, Ix>(cd, cd.pf, nsteps, par);
 }
 
 // flips the per-case lattice parity after a launch of an odd number of steps
@@ -466,6 +456,7 @@ struct lbm_batch {
     std::vector<int> nblk;
     CaseDesc *d_cases = nullptr;
     int *d_order = nullptr, *d_parity = nullptr;
+    bool far = false;                // a D2Q9 case has far_arrays (D3Q27 cases are refused before that size)
     int n2 = 0, n3 = 0;              // cases per lattice; d_order lists the D2Q9 cases first
     std::vector<void *> allocs;
     double *partials = nullptr, *io = nullptr, *rscratch = nullptr;
@@ -527,9 +518,9 @@ void launch_phase(lbm_batch *b, int st) {
         if (b->nw3) hipLaunchKernelGGL(kern3, dim3(b->nw3), tb, 0, b->stream, b->d_cases, b->d_work3, st, b->d_parity);
     };
     switch (b->split.npt) {
-    case 1: go(k_batch_phase<2, PHASE, 1>, k_batch_phase<3, PHASE, 1>); break;
-    case 2: go(k_batch_phase<2, PHASE, 2>, k_batch_phase<3, PHASE, 2>); break;
-    default: go(k_batch_phase<2, PHASE, 4>, k_batch_phase<3, PHASE, 4>); break;
+    case 1: go(b->far ? k_batch_phase<2, PHASE, 1, size_t> : k_batch_phase<2, PHASE, 1>, k_batch_phase<3, PHASE, 1>); break;
+    case 2: go(b->far ? k_batch_phase<2, PHASE, 2, size_t> : k_batch_phase<2, PHASE, 2>, k_batch_phase<3, PHASE, 2>); break;
+    default: go(b->far ? k_batch_phase<2, PHASE, 4, size_t> : k_batch_phase<2, PHASE, 4>, k_batch_phase<3, PHASE, 4>); break;
     }
 }
 
@@ -557,7 +548,7 @@ int launch(lbm_batch *b, int nsteps, int block) {
         return hipGetLastError() == hipSuccess ? LBM_OK : LBM_E_HIP;
     }
     if (b->n2)
-        hipLaunchKernelGGL(k_batch<2>, dim3(b->n2), dim3(block), 0, b->stream, b->d_cases, b->d_order, nc, nsteps,
+        hipLaunchKernelGGL((b->far ? k_batch<2, size_t> : k_batch<2>), dim3(b->n2), dim3(block), 0, b->stream, b->d_cases, b->d_order, nc, nsteps,
                            b->d_parity);
     if (b->n3)
         hipLaunchKernelGGL(k_batch<3>, dim3(b->n3), dim3(block < 256 ? block : 256), 0, b->stream, b->d_cases, b->d_order + b->n2, nc,
@@ -756,6 +747,7 @@ int lbm_batch_create(const lbm_params *cases, int ncases, lbm_batch **out) {
         }
         b->params[c].mask = nullptr;
         b->params[c].rho_wall_field = nullptr;
+        b->far = b->far || far_arrays(cd.g, cd.fp64);
         b->ks[c] = kernel_set(cd.D, cd.fp64, cd.mask != nullptr, far_arrays(cd.g, cd.fp64));
         if (cd.mask) b->ks[c].links(b->stream, cd.mask, cd.links, cd.g);
         b->nblk[c] = moment_block_count(cd.D, cd.g);
