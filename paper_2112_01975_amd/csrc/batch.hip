@@ -51,12 +51,18 @@ struct CaseDesc {
 };
 
 // --------------------------------------------------------------- device part
+// Instances of the kernels: no case has solid nodes (the pulls at walls take registers, so waves,
+// from the others), some have, or one has populations past 4 GiB (far_arrays).
+struct Plain { static constexpr bool walls = false; using index = unsigned; };
+struct Walls { static constexpr bool walls = true; using index = unsigned; };
+struct Far { static constexpr bool walls = true; using index = size_t; };
+
 // The per-node step functions see a case through a view: node indices, solid flags, the
 // pull gather, the field arrays, 1- and 2-ring neighbour indices and the store. GlobalView
 // addresses the case's device arrays; TileView a tile of a D2Q9 case held in LDS. Both
 // designs run the same arithmetic in the same order, so they give the same bits.
-// (Ix: index type of the populations; size_t for arrays past 4 GiB)
-template <int D, class S, class C, class Ix> struct GlobalView {
+// K: what the batch needs of the kernel (Plain, Walls or Far below).
+template <int D, class S, class C, class K> struct GlobalView {
     const Geom &g;
     const uint8_t *mask;
     const S *A;
@@ -70,11 +76,11 @@ template <int D, class S, class C, class Ix> struct GlobalView {
         const int x = n % g.nx, t = n / g.nx, y = t % g.ny, z = t / g.ny;
         return Node{x, y, z, Nbr<D>(g, x, y, z)};
     }
-    __device__ __forceinline__ bool solid(int n) const { return mask && mask[n]; }
+    __device__ __forceinline__ bool solid(int n) const { return K::walls && mask && mask[n]; }
     __device__ __forceinline__ int global_index(int n) const { return n; }
     __device__ __forceinline__ void gather_at(const Node &nd, int n, C (&h)[Lat<D>::Q]) const {
-        if (mask) gather<D, S, C, true, Ix>(A, g.qs, mask, nd.nb, n, h);
-        else gather<D, S, C, false, Ix>(A, g.qs, mask, nd.nb, n, h);
+        if (K::walls && mask) gather<D, S, C, true, typename K::index>(A, g.qs, mask, nd.nb, n, h);
+        else gather<D, S, C, false, typename K::index>(A, g.qs, mask, nd.nb, n, h);
     }
     __device__ __forceinline__ int at1(const Node &nd, int cx, int cy, int cz) const { return nd.nb.at(cx, cy, cz); }
     __device__ __forceinline__ int at2(const Node &nd, int cx, int cy, int cz) const {
@@ -85,7 +91,7 @@ template <int D, class S, class C, class Ix> struct GlobalView {
     __device__ __forceinline__ C &rho(int n) const { return frho[n]; }
     __device__ __forceinline__ C &psi(int n) const { return fpsi[n]; }
     __device__ __forceinline__ C &gfield(int a, int n) const { return fg[a * g.N + n]; }
-    __device__ __forceinline__ void store(int i, int n, C v) const { st_at(B + i * g.qs, (Ix)n, S(v)); }
+    __device__ __forceinline__ void store(int i, int n, C v) const { st_at(B + i * g.qs, (typename K::index)n, S(v)); }
 };
 
 // phase 1 at node n (view coordinates nd): rho, signed psi and g = rho u^3 of the current
@@ -163,20 +169,20 @@ __device__ __forceinline__ void phase2_at(const V &v, const Params<C> &p, int n,
     });
 }
 
-template <int D, class S, class C, class Ix>
-__device__ __forceinline__ GlobalView<D, S, C, Ix> global_view(const CaseDesc &cd, const S *A, S *B) {
-    return GlobalView<D, S, C, Ix>{cd.g, cd.mask, A, B, (C *)cd.frho, (C *)cd.fpsi, (C *)cd.fg};
+template <int D, class S, class C, class K>
+__device__ __forceinline__ GlobalView<D, S, C, K> global_view(const CaseDesc &cd, const S *A, S *B) {
+    return GlobalView<D, S, C, K>{cd.g, cd.mask, A, B, (C *)cd.frho, (C *)cd.fpsi, (C *)cd.fg};
 }
 
-template <int D, class S, class C, class Ix>
+template <int D, class S, class C, class K>
 __device__ __forceinline__ void phase1_node(const CaseDesc &cd, const Params<C> &p, const S *A, int n) {
-    const auto v = global_view<D, S, C, Ix>(cd, A, nullptr);
+    const auto v = global_view<D, S, C, K>(cd, A, nullptr);
     phase1_at<D, S, C>(v, p, n, v.node(n));
 }
 
-template <int D, class S, class C, class Ix>
+template <int D, class S, class C, class K>
 __device__ __forceinline__ void phase2_node(const CaseDesc &cd, const Params<C> &p, const S *A, S *B, int n) {
-    const auto v = global_view<D, S, C, Ix>(cd, A, B);
+    const auto v = global_view<D, S, C, K>(cd, A, B);
     if (!v.solid(n)) phase2_at<D, S, C>(v, p, n, v.node(n));
 }
 
@@ -333,16 +339,16 @@ __global__ __launch_bounds__(4 * CL) void k_batch_tile(const CaseDesc *__restric
 }
 
 // the whole step loop of one case in one workgroup (persistent design)
-template <int D, class S, class C, class Ix>
+template <int D, class S, class C, class K>
 __device__ void case_steps(const CaseDesc &cd, const Params<C> &p, int nsteps, int parity) {
     S *L0 = (S *)cd.A, *L1 = (S *)cd.B;
     for (int st = 0; st < nsteps; ++st) {
         const bool even = ((st + parity) & 1) == 0;
         const S *A = even ? L0 : L1;
         S *B = even ? L1 : L0;
-        for (int n = threadIdx.x; n < cd.g.N; n += blockDim.x) phase1_node<D, S, C, Ix>(cd, p, A, n);
+        for (int n = threadIdx.x; n < cd.g.N; n += blockDim.x) phase1_node<D, S, C, K>(cd, p, A, n);
         __syncthreads();
-        for (int n = threadIdx.x; n < cd.g.N; n += blockDim.x) phase2_node<D, S, C, Ix>(cd, p, A, B, n);
+        for (int n = threadIdx.x; n < cd.g.N; n += blockDim.x) phase2_node<D, S, C, K>(cd, p, A, B, n);
         __syncthreads();
     }
 }
@@ -358,7 +364,7 @@ struct Work {
 };
 constexpr int kStepMaxBlock = 256;   // largest threads per block of the stepped kernels
 
-template <int D, int PHASE, int NPT, class Ix = unsigned>
+template <int D, int PHASE, int NPT, class K>
 __global__ __launch_bounds__(kStepMaxBlock) void k_batch_phase(const CaseDesc *__restrict__ cases,
                                                                const Work *__restrict__ work, int st,
                                                                const int *__restrict__ parity) {
@@ -375,8 +381,8 @@ __global__ __launch_bounds__(kStepMaxBlock) void k_batch_phase(const CaseDesc *_
         for (int m = 0; m < NPT; ++m) {
             const int n = n0 + m * stride;
             if (n >= cd.g.N) break;
-            if constexpr (PHASE == 1) phase1_node<D, double, double, Ix>(cd, cd.pd, A, n);
-            else phase2_node<D, double, double, Ix>(cd, cd.pd, A, B, n);
+            if constexpr (PHASE == 1) phase1_node<D, double, double, K>(cd, cd.pd, A, n);
+            else phase2_node<D, double, double, K>(cd, cd.pd, A, B, n);
         }
     } else {
         const float *A = (const float *)(even ? cd.A : cd.B);
@@ -385,8 +391,8 @@ __global__ __launch_bounds__(kStepMaxBlock) void k_batch_phase(const CaseDesc *_
         for (int m = 0; m < NPT; ++m) {
             const int n = n0 + m * stride;
             if (n >= cd.g.N) break;
-            if constexpr (PHASE == 1) phase1_node<D, float, float, Ix>(cd, cd.pf, A, n);
-            else phase2_node<D, float, float, Ix>(cd, cd.pf, A, B, n);
+            if constexpr (PHASE == 1) phase1_node<D, float, float, K>(cd, cd.pf, A, n);
+            else phase2_node<D, float, float, K>(cd, cd.pf, A, B, n);
         }
     }
 }
@@ -399,15 +405,15 @@ constexpr Split kSplits[] = {{256, 1}, {128, 1}, {64, 1}, {256, 2}, {128, 2}, {6
 
 // one kernel per lattice: the register budget of a D2Q9 sweep is not set by the D3Q27 body
 // (D3Q27 cases run with at most 256 threads, which leaves room for the 27-population body)
-template <int D, class Ix = unsigned>
+template <int D, class K>
 __global__ __launch_bounds__(D == 2 ? 1024 : 256) void k_batch(const CaseDesc *__restrict__ cases, const int *__restrict__ order,
                                                  int ncases, int nsteps, const int *__restrict__ parity) {
     const int c = order[blockIdx.x];
     if (c >= ncases) return;
     const CaseDesc cd = cases[c];
     const int par = parity[c];
-    if (cd.fp64) case_steps<D, double, double, Ix>(cd, cd.pd, nsteps, par);
-    else case_steps<D, float, float, Ix>(cd, cd.pf, nsteps, par);
+    if (cd.fp64) case_steps<D, double, double, K>(cd, cd.pd, nsteps, par);
+    else case_steps<D, float, float, K>(cd, cd.pf, nsteps, par);
 }
 
 // flips the per-case lattice parity after a launch of an odd number of steps
@@ -457,6 +463,7 @@ struct lbm_batch {
     CaseDesc *d_cases = nullptr;
     int *d_order = nullptr, *d_parity = nullptr;
     bool far = false;                // a D2Q9 case has far_arrays (D3Q27 cases are refused before that size)
+    bool walls = false;              // a case has solid nodes
     int n2 = 0, n3 = 0;              // cases per lattice; d_order lists the D2Q9 cases first
     std::vector<void *> allocs;
     double *partials = nullptr, *io = nullptr, *rscratch = nullptr;
@@ -518,9 +525,12 @@ void launch_phase(lbm_batch *b, int st) {
         if (b->nw3) hipLaunchKernelGGL(kern3, dim3(b->nw3), tb, 0, b->stream, b->d_cases, b->d_work3, st, b->d_parity);
     };
     switch (b->split.npt) {
-    case 1: go(b->far ? k_batch_phase<2, PHASE, 1, size_t> : k_batch_phase<2, PHASE, 1>, k_batch_phase<3, PHASE, 1>); break;
-    case 2: go(b->far ? k_batch_phase<2, PHASE, 2, size_t> : k_batch_phase<2, PHASE, 2>, k_batch_phase<3, PHASE, 2>); break;
-    default: go(b->far ? k_batch_phase<2, PHASE, 4, size_t> : k_batch_phase<2, PHASE, 4>, k_batch_phase<3, PHASE, 4>); break;
+    case 1: go(b->far ? k_batch_phase<2, PHASE, 1, Far> : b->walls ? k_batch_phase<2, PHASE, 1, Walls> : k_batch_phase<2, PHASE, 1, Plain>,
+               b->walls ? k_batch_phase<3, PHASE, 1, Walls> : k_batch_phase<3, PHASE, 1, Plain>); break;
+    case 2: go(b->far ? k_batch_phase<2, PHASE, 2, Far> : b->walls ? k_batch_phase<2, PHASE, 2, Walls> : k_batch_phase<2, PHASE, 2, Plain>,
+               b->walls ? k_batch_phase<3, PHASE, 2, Walls> : k_batch_phase<3, PHASE, 2, Plain>); break;
+    default: go(b->far ? k_batch_phase<2, PHASE, 4, Far> : b->walls ? k_batch_phase<2, PHASE, 4, Walls> : k_batch_phase<2, PHASE, 4, Plain>,
+               b->walls ? k_batch_phase<3, PHASE, 4, Walls> : k_batch_phase<3, PHASE, 4, Plain>); break;
     }
 }
 
@@ -548,10 +558,10 @@ int launch(lbm_batch *b, int nsteps, int block) {
         return hipGetLastError() == hipSuccess ? LBM_OK : LBM_E_HIP;
     }
     if (b->n2)
-        hipLaunchKernelGGL((b->far ? k_batch<2, size_t> : k_batch<2>), dim3(b->n2), dim3(block), 0, b->stream, b->d_cases, b->d_order, nc, nsteps,
+        hipLaunchKernelGGL((b->far ? k_batch<2, Far> : b->walls ? k_batch<2, Walls> : k_batch<2, Plain>), dim3(b->n2), dim3(block), 0, b->stream, b->d_cases, b->d_order, nc, nsteps,
                            b->d_parity);
     if (b->n3)
-        hipLaunchKernelGGL(k_batch<3>, dim3(b->n3), dim3(block < 256 ? block : 256), 0, b->stream, b->d_cases, b->d_order + b->n2, nc,
+        hipLaunchKernelGGL((b->walls ? k_batch<3, Walls> : k_batch<3, Plain>), dim3(b->n3), dim3(block < 256 ? block : 256), 0, b->stream, b->d_cases, b->d_order + b->n2, nc,
                            nsteps, b->d_parity);
     if (nsteps & 1)
         hipLaunchKernelGGL(k_flip_parity, fg, dim3(256), 0, b->stream, b->d_parity, b->d_tiled, nc, nsteps, nsteps);
@@ -747,6 +757,7 @@ int lbm_batch_create(const lbm_params *cases, int ncases, lbm_batch **out) {
         }
         b->params[c].mask = nullptr;
         b->params[c].rho_wall_field = nullptr;
+        b->walls = b->walls || cd.mask;
         b->far = b->far || far_arrays(cd.g, cd.fp64);
         b->ks[c] = kernel_set(cd.D, cd.fp64, cd.mask != nullptr, far_arrays(cd.g, cd.fp64));
         if (cd.mask) b->ks[c].links(b->stream, cd.mask, cd.links, cd.g);
