@@ -722,6 +722,7 @@ int lbm_batch_create(const lbm_params *cases, int ncases, lbm_batch **out) {
         return q;
     };
     int max_nblk = 0;
+    size_t link_words = 0;
     for (int c = 0; c < ncases; ++c) {
         const lbm_params &p = cases[c];
         CaseDesc &cd = b->host[c];
@@ -744,8 +745,7 @@ int lbm_batch_create(const lbm_params *cases, int ncases, lbm_batch **out) {
             uint8_t *m = (uint8_t *)dalloc(N);
             if (!m || hipMemcpy(m, p.mask, N, hipMemcpyHostToDevice) != hipSuccess) { free_batch(b); return bfail(nullptr, LBM_E_HIP, "mask upload failed"); }
             cd.mask = m;
-            cd.links = (uint32_t *)dalloc(N * sizeof(uint32_t));
-            if (!cd.links) { free_batch(b); return bfail(nullptr, LBM_E_NOMEM, "device allocation failed"); }
+            link_words += (N + 63) / 64 * 64;
         }
         if (p.rho_wall_field) {   // per-node wall densities of this case
             void *w = cd.fp64 ? (void *)upload_wall_field<double>(p.rho_wall_field, cd.g)
@@ -760,10 +760,20 @@ int lbm_batch_create(const lbm_params *cases, int ncases, lbm_batch **out) {
         b->walls = b->walls || cd.mask;
         b->far = b->far || far_arrays(cd.g, cd.fp64);
         b->ks[c] = kernel_set(cd.D, cd.fp64, cd.mask != nullptr, far_arrays(cd.g, cd.fp64));
-        if (cd.mask) b->ks[c].links(b->stream, cd.mask, cd.links, cd.g);
         b->nblk[c] = moment_block_count(cd.D, cd.g);
         max_nblk = std::max(max_nblk, b->nblk[c]);
         b->io_elems = std::max(b->io_elems, (size_t)(1 + cd.D) * N);
+    }
+    if (link_words) {   // solid-neighbour bits of all cases in one block, made with no copies between
+        uint32_t *at = (uint32_t *)dalloc(link_words * sizeof(uint32_t));
+        if (!at) { free_batch(b); return bfail(nullptr, LBM_E_NOMEM, "device allocation failed"); }
+        for (int c = 0; c < ncases; ++c) {
+            CaseDesc &cd = b->host[c];
+            if (!cd.mask) continue;
+            cd.links = at;
+            at += ((size_t)cd.g.N + 63) / 64 * 64;
+            b->ks[c].links(b->stream, cd.mask, cd.links, cd.g);
+        }
     }
     b->d_cases = (CaseDesc *)dalloc(ncases * sizeof(CaseDesc));
     b->d_order = (int *)dalloc(ncases * sizeof(int));
