@@ -1,11 +1,13 @@
 // host_copy.hip -- pageable copies through pinned buffers and worker threads.
 #include <hip/hip_runtime.h>
 #include <sched.h>
+#include <stdio.h>
 #include <string.h>
 
 #include <algorithm>
 #include <atomic>
 #include <mutex>
+#include <string>
 #include <thread>
 #include <vector>
 
@@ -30,9 +32,16 @@ bool g_busy = false;        // one staged copy at a time; another thread's copy 
 char *g_buf = nullptr;      // a chunk for each worker
 
 int worker_count() {
+    static const std::string quota = [] {   // this process's limit; a container sees its own group at the root
+        char text[64] = "";
+        if (FILE *f = fopen("/sys/fs/cgroup/cpu.max", "r")) {
+            if (!fgets(text, sizeof text, f)) text[0] = 0;
+            fclose(f);
+        }
+        return std::string(text);
+    }();
     cpu_set_t set;
-    const int cpus = sched_getaffinity(0, sizeof set, &set) == 0 ? CPU_COUNT(&set) : 1;
-    return std::max(1, std::min(kWorkers, cpus / 2));
+    return workers_for(sched_getaffinity(0, sizeof set, &set) == 0 ? CPU_COUNT(&set) : 1, quota.c_str());
 }
 
 // allocation and waits here leave a capture on another thread's stream alone
@@ -93,6 +102,13 @@ bool capturing(hipStream_t s) {
 }
 
 }  // namespace
+
+int workers_for(int cpus, const char *cpu_max) {
+    long long quota = 0, period = 0;
+    if (sscanf(cpu_max, "%lld %lld", &quota, &period) == 2 && quota > 0 && period > 0)
+        cpus = (int)std::min<long long>(cpus, quota / period);
+    return std::max(1, std::min(kWorkers, cpus / 2));
+}
 
 void staging_hold() {
     std::lock_guard<std::mutex> lk(g_mu);

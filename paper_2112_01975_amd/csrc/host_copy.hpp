@@ -16,6 +16,10 @@ namespace lbm {
 // 35 GB/s either way.
 hipError_t copy_pageable(int dev, hipStream_t stream, void *dst, const void *src, size_t bytes, hipMemcpyKind kind);
 
+// Worker threads for `cpus` CPUs of the affinity mask under a control group's quota, the text of its
+// cpu.max ("max" or microseconds, then the period; "" without one).
+int workers_for(int cpus, const char *cpu_max);
+
 // The pinned buffer is shared by all contexts of a process, 16 MiB; it is freed when the last
 // holder lets go.
 void staging_hold();

@@ -151,6 +151,12 @@ int main(int argc, char **argv) {
             for (const auto &t : copies) n += t.second;
             EXPECT((n == 1) == c.direct);
         }
+    } else if (check == "quota") {
+        // half the CPUs, of the affinity mask or of the control group's quota, eight at most
+        EXPECT(workers_for(16, "max 100000\n") == 8 && workers_for(256, "1600000 100000\n") == 8);
+        EXPECT(workers_for(256, "400000 100000\n") == 2 && workers_for(256, "250000 100000\n") == 1);
+        EXPECT(workers_for(4, "") == 2 && workers_for(1, "max 100000\n") == 1 && workers_for(6, "garbage") == 3);
+        EXPECT(workers_for(64, "0 0\n") == 8 && workers_for(64, "50000 100000\n") == 1);
     } else if (check == "per_thread_stream") {
         // that handle names another stream in every thread: only the caller's is the one meant
         EXPECT(round_trip(hipStreamPerThread) == 1);

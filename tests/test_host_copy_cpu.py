@@ -25,7 +25,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("check", ["data", "worth_the_threads", "per_thread_stream", "current_device", "block", "block_to_device", "no_pinned_memory", "capture_mode"])
+@pytest.mark.parametrize("check", ["data", "worth_the_threads", "quota", "per_thread_stream", "current_device", "block", "block_to_device", "no_pinned_memory", "capture_mode"])
 def test_copies_through_worker_threads(driver, check):
     r = subprocess.run([driver, check], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and "copy driver ok" in r.stdout, (r.stdout + r.stderr)[-4000:]
