@@ -20,11 +20,12 @@ namespace {
 constexpr int kWorkers = 8;
 constexpr size_t kChunk = size_t(2) << 20;
 // Copies of up to this many bytes go directly: the workers' threads, and for a process's first
-// large copy the pinning, would take longer. ms, direct | workers | workers, pinning included:
-//   to the device    5 MB 0.15 | 0.21 | 0.30   16 MB 0.44 | 0.53 | 0.69   32 MB 0.87 | 0.99 | 1.21   48 MB 1.64 | 1.40 | 1.60
-//   to the host      5 MB 0.27 | 0.20 | 0.30    6 MB 0.33 | 0.24 | 0.29   16 MB 0.90 | 0.54 | 0.65   48 MB 2.77 | 1.33 | 1.50
-// (to a fresh array of 48 MB 4.69 | 1.42 | 1.51; chunks of 1 MiB 48 MB 1.62, 512 KiB 2.30)
-constexpr size_t least(hipMemcpyKind kind) { return kind == hipMemcpyHostToDevice ? size_t(38) << 20 : size_t(6) << 20; }
+// large copy the pinning, would take longer. ms, direct | workers (the pinning is 0.05 to 0.2 more):
+//   to the device, array in the CPU's caches   5 MB 0.15 | 0.22   16 MB 0.45 | 0.54   32 MB 0.88 | 0.94   48 MB 1.56 | 1.34
+//                  array in memory             8 MB 0.30 | 0.38   16 MB 0.58 | 0.58   24 MB 0.84 | 0.80   48 MB 1.67 | 1.42
+//   to the host    5 MB 0.27 | 0.20    6 MB 0.33 | 0.24    16 MB 0.90 | 0.54    48 MB 2.77 | 1.33
+// (to a fresh array of 48 MB 4.69 | 1.42; chunks of 1 MiB 48 MB 1.62, 512 KiB 2.30)
+constexpr size_t least(hipMemcpyKind kind) { return kind == hipMemcpyHostToDevice ? size_t(20) << 20 : size_t(6) << 20; }
 
 std::mutex g_mu;            // holders and the buffer
 int g_holders = 0;

@@ -7,11 +7,11 @@
 namespace lbm {
 
 // Copies `bytes` between pageable host memory and device `dev` on `stream`, one of that device.
-// The caller's current device stays as it is. Copies of more than 38 MiB to the device and 6 MiB to
+// The caller's current device stays as it is. Copies of more than 20 MiB to the device and 6 MiB to
 // the host are complete on return; smaller ones, those of memory that is not pageable, those on
 // hipStreamPerThread and those into a capture go to hipMemcpyAsync. The runtime's own copy of
 // pageable memory goes through one thread, 18 GB/s to the host (10 into fresh arrays) and 29 to the
-// device past 40 MB; here worker threads take turns on the stream, each with a pinned 2 MiB of its
+// device from memory; here worker threads take turns on the stream, each with a pinned 2 MiB of its
 // own, so that one's transfer overlaps the others' copies (and the page faults of a fresh array):
 // 35 GB/s either way.
 hipError_t copy_pageable(int dev, hipStream_t stream, void *dst, const void *src, size_t bytes, hipMemcpyKind kind);

@@ -139,10 +139,10 @@ int main(int argc, char **argv) {
         (void)round_trip((hipStream_t) nullptr);
     } else if (check == "worth_the_threads") {
         // one direct copy up to the sizes from which the workers are faster, several beyond
-        std::vector<char> a(size_t(41) << 20), b(a.size());
+        std::vector<char> a(size_t(21) << 20), b(a.size());
         const struct { size_t mib; hipMemcpyKind kind; bool direct; } cases[] = {
-            {1, hipMemcpyHostToDevice, true}, {5, hipMemcpyHostToDevice, true}, {38, hipMemcpyHostToDevice, true},
-            {41, hipMemcpyHostToDevice, false}, {1, hipMemcpyDeviceToHost, true}, {6, hipMemcpyDeviceToHost, true},
+            {1, hipMemcpyHostToDevice, true}, {5, hipMemcpyHostToDevice, true}, {20, hipMemcpyHostToDevice, true},
+            {21, hipMemcpyHostToDevice, false}, {1, hipMemcpyDeviceToHost, true}, {6, hipMemcpyDeviceToHost, true},
             {7, hipMemcpyDeviceToHost, false}};
         for (const auto &c : cases) {
             copies.clear();

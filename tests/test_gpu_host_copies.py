@@ -153,7 +153,7 @@ def test_batch_moments_into_device_and_pinned_arrays():
         P.lbm_batch_destroy(b)
 
 
-# fields and populations of more than 38 MiB each, which go up through the workers too; padded rows
+# fields and populations of more than 20 MiB each, which go up through the workers too; padded rows
 @pytest.mark.parametrize("dims,prec", [((192, 176, 170), 0), ((250, 240, 190), 1)])
 def test_large_uploads(dims, prec):
     import paper_2112_01975_amd as P
