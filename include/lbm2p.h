@@ -143,15 +143,15 @@ int lbm_init_fields(lbm_ctx *c, const double *rho, const double *u);
 /* Advances n time steps of eq LBGK (stream-collide with the Korteweg force and
  * halfway, or with link_q interpolated, bounce-back at solid nodes). Runs the FP64 watchdog as selected by
  * check_every; returns LBM_E_DIVERGED / LBM_E_DOMAIN when it trips. When no
- * check runs, the call only enqueues work on the context stream. D2Q9 advances tiles by one
- * to three steps per launch; a D3Q27 step is the fused z-march, or on grids too small for it the
- * moment pass and then the collide (LBM2P_TWO_PASS=1 takes the latter for both lattices; in
- * D2Q9 the two agree to rounding). Results do not depend, bit for bit, on how a run is cut into
- * calls. Contexts off the fused D3Q27 step capture about 32 steps into a HIP graph on the first
- * call with at least as many between two checks. Such runs then replay that graph on the
- * context stream, with results identical bit for bit; the capture uses the context's own stream.
- * Launches are made one by one when the context stream is itself being captured, or when the
- * environment sets LBM2P_GRAPH=0. The two lattices swap roles once per step either way. */
+ * check runs, the call only enqueues work on the context stream. D2Q9 advances tiles by two or
+ * three steps per launch, or the grid by one with a thread per node; a D3Q27 step is the fused
+ * z-march, or on grids too small for it the moment pass and then the collide (LBM2P_TWO_PASS=1
+ * takes the latter for both lattices; in D2Q9 the two agree to rounding). Results do not depend,
+ * bit for bit, on how a run is cut into calls. Contexts off the fused D3Q27 step capture about 32
+ * steps into a HIP graph on the first call with at least as many between two checks. Such runs
+ * then replay that graph on the context stream, with results identical bit for bit; the capture
+ * uses the context's own stream. Launches are made one by one when the context stream is itself
+ * being captured, or when the environment sets LBM2P_GRAPH=0. The two lattices swap roles once per step either way. */
 int lbm_step(lbm_ctx *c, int64_t n);
 
 /* Density and velocity of the current state. rho: host [N] (nullable); U: host
@@ -286,7 +286,8 @@ int lbm_kappa_for_width(const lbm_params *p, double width, double *kappa);
  * GPU target and case list. Interpolated walls (link_q) and cases with (D+1) N >= 2^31 are
  * rejected with LBM_E_INVAL. At its end lbm_batch_step checks every case for divergence in
  * one pass over all cases (non-finite stored populations at fluid nodes): LBM_E_DIVERGED names
- * the first such case. */
+ * the first such case. lbm_batch_moments fills rho [N], U [D][N] (host or device arrays) and
+ * totals (host), each nullable, and waits for them. */
 int lbm_batch_create(const lbm_params *cases, int ncases, lbm_batch **out);
 int lbm_batch_init_fields(lbm_batch *b, int icase, const double *rho, const double *u);
 int lbm_batch_step(lbm_batch *b, int64_t n);

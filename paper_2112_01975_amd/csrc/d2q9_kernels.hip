@@ -95,8 +95,8 @@ __device__ __forceinline__ void update_node(const Params<C> &p, const C (&gw)[8]
 // Bound by the vector instructions of the nodes and their halo, with the launch itself on small
 // grids: per launch of two steps of 32 x 32 tiles (512^2 FP32, 10 us) 1 us prologue, 2.5 us pulls,
 // 2.5 us first step, 2.5 us second step, 2 us gap to the next launch. What a step costs is its
-// instruction count, so the force takes differences before factors, the update gathers its
-// terms by axis (collide_plane), and constants sit in vector registers. Holding a frame of
+// instruction count, so constants sit in vector registers, and in FP64 the force takes differences
+// before factors and the update gathers its terms by axis (collide_plane). Holding a frame of
 // populations in LDS, loaded with 16-byte copies, was slower (5.5 against 5.1 us a step).
 template <class S, class C, bool MASK, int NT, int NPT>
 __global__ __launch_bounds__(NT) void k_d2q9(const S *__restrict__ A, S *__restrict__ B, Geom g,
@@ -237,8 +237,9 @@ __global__ __launch_bounds__(NT) void k_d2q9(const S *__restrict__ A, S *__restr
 // One step per launch on a 64 x 8 tile, one thread per tile node, 304 of which also pull one node of
 // the two-node halo. Only the tile's own nodes are collided and kept in registers, and two
 // workgroups share a CU, so this moves a large FP64 grid faster than the tiles above, whose
-// recomputed halo costs more there than the launches and traffic they save: 2040x1900 FP64 121 us
-// a step, 4.6 TB/s of populations against 5.4 for a copy, and 126 in tiles. NT: see d2_stream.
+// recomputed halo costs more there than the launches and traffic they save: 2040x1900 FP64 115 to
+// 121 us a step (by placement in memory), 4.6 to 4.9 TB/s of populations against 5.4 for a copy, and
+// 126 in tiles. NT: see d2_stream.
 constexpr int SX = 64, SY = 8, SHALO = 2;
 template <class S, class C, bool MASK, class Ix, bool NT>
 __global__ __launch_bounds__(SX *SY) void k_d2q9_single(const S *__restrict__ A, S *__restrict__ B, Geom g,

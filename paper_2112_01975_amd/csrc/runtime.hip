@@ -414,8 +414,10 @@ int lbm_create(const lbm_params *p, lbm_ctx **out) {
     // 64 x 4 x 2 tiles where many are idle; near the line, single pass | two passes, us per step:
     // 64^3 FP32 37 | 25, FP64 57 | 50; 96^3 FP32 70 | 82, FP64 153 | 195; 16x16x4096 FP32 95 | 210,
     // FP64 333 | 580; 8x300x300 FP32 131 | 292, FP64 483 | 813; 33x129x257 FP64 236 | 334. With
-    // walls, whose planes cost more, the line is 16-plane chunks for every CU. LBM2P_FUSED=1
-    // takes the single-pass step at any size.
+    // walls, whose planes cost more, the line is 16-plane chunks for every CU; FP32, FP64 with
+    // halfway walls: 64^3 65 | 29, 108 | 53; 96^3 111 | 106, 206 | 207; 128^3 160 | 195, 333 | 434
+    // (112^3, below the line, 135 | 156 and 266 | 319). LBM2P_FUSED=1 takes the single-pass step at
+    // any size.
     const bool plain_box = c->D == 3 && !c->masked;
     const int nzg = c->g.nz;
     long long nz64 = 1, nz32 = 1;
