@@ -151,7 +151,8 @@ int lbm_init_fields(lbm_ctx *c, const double *rho, const double *u);
  * steps into a HIP graph on the first call with at least as many between two checks. Such runs
  * then replay that graph on the context stream, with results identical bit for bit; the capture
  * uses the context's own stream. Launches are made one by one when the context stream is itself
- * being captured, or when the environment sets LBM2P_GRAPH=0. The two lattices swap roles once per step either way. */
+ * being captured, or when the environment sets LBM2P_GRAPH=0. The two lattices swap roles once
+ * per step either way. */
 int lbm_step(lbm_ctx *c, int64_t n);
 
 /* Density and velocity of the current state. rho: host [N] (nullable); U: host
